@@ -1054,12 +1054,13 @@ __global__ void __launch_bounds__(64)
                     (int)threadIdx.x);
 }
 
+// 1 / d in FP64: the hardware estimate (2^-22 or better) and one cubic
+// correction, r (1 + e + e^2) with e = 1 - d r, which leaves e^3 < 2^-64:
+// three fused multiply-adds where two Newton-Raphson steps take four.
 __device__ __forceinline__ double rcp64(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  double e = fma(-d, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-d, r, 1.0);
-  return fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 
 __device__ __forceinline__ int pow2_at_least(int n) {
@@ -1069,154 +1070,308 @@ __device__ __forceinline__ int pow2_at_least(int n) {
 }
 
 constexpr int kStage = 128;  // U-list sources staged in LDS per pass
+constexpr int kFarItems = 8;  // expansions staged in LDS per pass (FP64 leaf kernel)
 
-// Potential at the targets of one leaf (one 64-lane block).  Lanes are
-// (target, slice): with tp = pow2 >= #targets (<= 32) the block has
-// S = 64 / tp slices, each taking every S-th staged source, W-list box and
-// ancestor; slices are summed by shuffles.  Work: the local expansions of
-// the leaf and its ancestors (level >= 2), M2P over its W list, the direct
-// sum over the gathered sources of its U list (self pair excluded by
-// d == 0), then the operator row assembly in API order.  FP64 version.
-template <int P>
-__global__ void __launch_bounds__(64, 8)
+// What the FP64 leaf kernel forms at a target.
+enum LeafMode {
+  kLeafField = 0,  // Re Psi for RB right-hand sides, then the assembled row
+  kLeafPsi = 1,    // Psi, complex
+  kLeafDeriv = 2   // Psi and Psi', complex
+};
+template <int MODE, int RB>
+constexpr int leaf_values() { return MODE == kLeafField ? RB : 2 * MODE; }
+
+// The near field of one leaf's targets [0, nt), nt <= 64, for K <= 4 targets
+// per lane: lanes are (target t mod tp, slice) with tp = 2^lg <= 16, lane
+// target t + tp k for k < K, and S = 64 W / tp slices, each taking every
+// S-th staged source.  A source is read from LDS once for the K targets of
+// a lane, whose reciprocal chains run side by side.  `fin` gets the partial
+// sums, one value c of every target at a time.
+template <int MODE, int RB, int K, typename Stage, typename Fin>
+__device__ __forceinline__ void near_field64(int nt, int lg, int utot, int stage_n,
+                                             const double *__restrict__ tx,
+                                             const double *__restrict__ ty,
+                                             const double2 *__restrict__ sz,
+                                             const double2 *__restrict__ sp, const Stage &stage,
+                                             const Fin &fin) {
+  constexpr int NF = leaf_values<MODE, RB>(), UN = K >= 4 ? 1 : K >= 2 ? 2 : 4;
+  const int tp = 1 << lg, S = (int)blockDim.x >> lg;
+  const int tl = threadIdx.x & (tp - 1), sl = threadIdx.x >> lg;
+  double zx[K], zy[K], f[K][NF];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int t = min(tl + tp * k, nt - 1);  // past the end: discarded
+    zx[k] = tx[t];
+    zy[k] = ty[t];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) f[k][c] = 0.0;
+  }
+  for (int q0 = 0; q0 < utot; q0 += stage_n) {
+    const int take = min(stage_n, utot - q0);
+    // padded to a multiple of S with sources of zero strength at the
+    // origin, which add 0 * rcp(|z|^2 + 1e-300) = 0
+    const int tpad = (take + S - 1) & ~(S - 1);  // S: a power of two
+    stage(q0, take, tpad);
+    __syncthreads();
+#pragma unroll UN
+    for (int q = sl; q < tpad; q += S) {
+      const double2 s2 = sz[q];
+      double2 p2[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) p2[r] = sp[q * RB + r];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const double dx = zx[k] - s2.x, dy = zy[k] - s2.y;
+        // |d|^2 + 1e-300: a target's own source (d = 0) contributes
+        // 0 * rcp(1e-300) = 0; any other |d|^2 above 1e-284 is unchanged
+        const double inv = rcp64(fma(dx, dx, fma(dy, dy, 1e-300)));
+        if constexpr (MODE == kLeafField && RB == 1) {
+          f[k][0] = fma(fma(p2[0].x, dx, p2[0].y * dy), inv, f[k][0]);
+        } else if constexpr (MODE == kLeafField) {
+          const double ux = dx * inv, uy = dy * inv;
+#pragma unroll
+          for (int r = 0; r < RB; ++r) f[k][r] = fma(p2[r].x, ux, fma(p2[r].y, uy, f[k][r]));
+        } else {
+          const cx<double> iv{dx * inv, -dy * inv};
+          const cx<double> t = cx<double>{p2[0].x, p2[0].y} * iv;
+          f[k][0] += t.x;
+          f[k][1] += t.y;
+          if constexpr (MODE == kLeafDeriv) {
+            const cx<double> d = t * iv;
+            f[k][2] -= d.x;
+            f[k][3] -= d.y;
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < NF; ++c) {
+    double v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = f[k][c];
+    fin(c, sl, tl, tp, S, v, std::integral_constant<int, K>{});
+  }
+}
+
+// Potential at the targets of one leaf (one work-group of W = blockDim / 64
+// waves): the leaf's local expansion and M2P over its W list with one lane
+// per (target, slice of the list), then the direct sum over the gathered
+// sources of its U list (near_field64; the self pair excluded by d == 0),
+// all parts joined in LDS by one lane per target, which writes the row:
+// kLeafField the assembled operator row in API order for the RB right-hand
+// sides blockIdx.y RB .. (those < nrhs), kLeafPsi / kLeafDeriv the complex
+// field (and derivative) of one right-hand side.  ufp, when set, replaces
+// the leaf's own U range (boxes' ranges into uf_idx).
+//
+// Bound by VALU issue at large node counts: 14 issue slots a pair (10 FP64
+// instructions, the reciprocal estimate four slots) over 218M pairs are 90
+// of its 161 us at 1.02M nodes (leaf 64).  One target per lane, which this
+// form replaces, read 32 bytes of LDS per pair and lane, as long as the
+// arithmetic takes, and read every expansion coefficient by a vector load
+// per lane: 184 us; 73 -> 28 us at 77k nodes and 45 -> 18 us at 20k, where
+// it left most of the chip idle.  Coefficients by scalar loads took 212 us
+// (a wave waits for each chunk), sources read one stage ahead 167 us.
+template <int P, int MODE, int RB>
+__global__ void __launch_bounds__(256, MODE == kLeafField && RB == 1 ? 6 : 3)
     k_leaf64(const LeafHdr *__restrict__ hdr,
              const double *__restrict__ cxv, const double *__restrict__ cyv,
              const double *__restrict__ rad,
              const double *__restrict__ tx, const double *__restrict__ ty,
              const int64_t *__restrict__ tperm,
+             const int64_t *__restrict__ ufp,
              const int32_t *__restrict__ uf_idx,
              const int32_t *__restrict__ w_src,
              const double *__restrict__ sx, const double *__restrict__ sy,
              const cx<double> *__restrict__ p, int64_t ns,
              const cx<double> *__restrict__ M,
-             const cx<double> *__restrict__ L, int nbox,
-             double *__restrict__ out, int64_t ldy, double scale,
+             const cx<double> *__restrict__ L, int nbox, int nrhs,
+             double *__restrict__ out, double *__restrict__ dout, int64_t ldy, double scale,
              Assembly as) {
-  __shared__ double2 sz[kStage];
-  __shared__ double2 sp[kStage];
-  constexpr int NC = 2;  // sub-chunks of <= 32 targets per pass over U
+  constexpr int NF = leaf_values<MODE, RB>();
+  // sources (kStage per wave: position, RB strengths), or the partial sums
+  extern __shared__ __align__(16) double sh[];
   const LeafHdr &hd = hdr[blockIdx.x];
   const int b = hd.b;
-  const int r = blockIdx.y;
-  const int lane = threadIdx.x;
-  const cx<double> *pr = p + (int64_t)r * ns;
-  const cx<double> *Mr = M + (int64_t)r * nbox * P;
-  const cx<double> *Lr = L + (int64_t)r * nbox * P;
+  const int r0 = blockIdx.y * RB, nr = min(RB, nrhs - r0);
+  const int tid = threadIdx.x, nth = blockDim.x, W = nth >> 6;
+  const int stage_n = kStage * min(W, 2);
+  double2 *sz = reinterpret_cast<double2 *>(sh), *sp = sz + stage_n;
   const int64_t tb0 = hd.t0, ntb = hd.nt;
-  const int64_t uf0 = hd.uf0;
-  const int utot = (int)(hd.uf1 - uf0);  // U-list sources of the leaf
+  const int64_t uf0 = ufp ? ufp[b] : hd.uf0;
+  const int utot = (int)((ufp ? ufp[b + 1] : hd.uf1) - uf0);  // U-list sources
   const int wb = hd.wb, we = hd.we;
   const bool has_local = hd.lev >= 2;
   const double ir_b = hd.ir, cx_b = hd.cx, cy_b = hd.cy;
-  for (int64_t tc0 = 0; tc0 < ntb; tc0 += 32 * NC) {
-    const int nt = (int)min<int64_t>(32 * NC, ntb - tc0);
-    const int nch = (nt + 31) / 32;
-    // sub-chunk c: targets [32 c, min(32 c + 32, nt)) on tp_c lanes times
-    // S_c = 64 / tp_c source slices, tp_c = min(32, next power of two)
-    int S[NC], sl[NC], ti[NC];
-    bool act[NC];
-    double zxs[NC], zys[NC], fld[NC];
-    int Smax = 1;
+  for (int64_t tc0 = 0; tc0 < ntb; tc0 += 64) {
+    const int nt = (int)min<int64_t>(64, ntb - tc0);
+    const double *txc = tx + tb0 + tc0, *tyc = ty + tb0 + tc0;
+    // far part: the items (the local expansion, then the W-list boxes)
+    // staged in LDS, `ni` at a time, with lanes (target, slice of items)
+    const int lgf = __builtin_ctz(pow2_at_least(nt)), Sf = nth >> lgf;
+    const int ft = tid & ((1 << lgf) - 1), fs = tid >> lgf;
+    double far[NF];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      S[c] = 64;
-      sl[c] = 0;
-      act[c] = false;
-      ti[c] = 0;
-      zxs[c] = zys[c] = fld[c] = 0.0;
-      if (c >= nch) continue;  // uniform
-      const int rem = nt - 32 * c;
-      const int tp = rem >= 32 ? 32 : pow2_at_least(rem);
-      const int lg = __builtin_ctz(tp);  // tp is a power of two
-      S[c] = 64 >> lg;
-      Smax = max(Smax, S[c]);
-      const int tl = lane & (tp - 1);
-      sl[c] = lane >> lg;
-      act[c] = 32 * c + tl < nt;
-      ti[c] = (int)tc0 + 32 * c + tl;
-      if (!act[c]) continue;
-      const int64_t i = tb0 + ti[c];
-      const double zx = tx[i], zy = ty[i];
-      zxs[c] = zx;
-      zys[c] = zy;
-      double field = 0.0;
-      if (sl[c] == 0 && has_local) {
-        const cx<double> w{(zx - cx_b) * ir_b, (zy - cy_b) * ir_b};
-        const cx<double> *La = Lr + (int64_t)b * P;
-        cx<double> acc = La[P - 1];
-        for (int l = P - 2; l >= 0; --l) acc = cfma(acc, w, La[l]);
-        field += acc.x;
-      }
-      for (int e = wb + sl[c]; e < we; e += S[c]) {
-        const int cw = w_src[e];
-        cx<double> d{zx - cxv[cw], zy - cyv[cw]};
-        cx<double> rho = rad[cw] * cinv(d);
-        const cx<double> *a = Mr + (int64_t)cw * P;
-        cx<double> acc = a[P - 1];
-        for (int k = P - 2; k >= 0; --k) acc = cfma(acc, rho, a[k]);
-        field += (acc * rho).x;
-      }
-      fld[c] = field;
-    }
-    {  // the leaf's U-list sources, kStage at a time
-      const int total = utot;
-      for (int q0 = 0; q0 < total; q0 += kStage) {
-        const int take = min(kStage, total - q0);
-        // pad to a multiple of Smax with sources of zero strength at the
-        // origin: they add 0 * rcp(|z|^2 + 1e-300) = 0
-        const int tpad = (take + Smax - 1) & ~(Smax - 1);  // Smax: power of two
-        for (int q = lane; q < tpad; q += 64) {
-          if (q < take) {
-            const int64_t j = uf_idx[uf0 + q0 + q];
-            sz[q] = make_double2(sx[j], sy[j]);
-            const cx<double> pj = pr[j];
-            sp[q] = make_double2(pj.x, pj.y);
+    for (int c = 0; c < NF; ++c) far[c] = 0.0;
+    const double zx = txc[min(ft, nt - 1)], zy = tyc[min(ft, nt - 1)];
+    double4 *geo = reinterpret_cast<double4 *>(sh);  // centre, rad or -1 / rad
+    cx<double> *co = reinterpret_cast<cx<double> *>(geo + kFarItems);
+    for (int i0 = has_local ? 0 : 1; i0 < 1 + we - wb; i0 += kFarItems) {
+      const int ni = min(kFarItems, 1 + we - wb - i0);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        if (r >= nr) continue;  // uniform
+        for (int x = tid; x < ni * P; x += nth) {
+          const int i = i0 + x / P, k = x % P;
+          co[x] = i == 0 ? L[((int64_t)(r0 + r) * nbox + b) * P + k]
+                         : M[((int64_t)(r0 + r) * nbox + w_src[wb + i - 1]) * P + k];
+        }
+        if (r == 0 && tid < ni) {
+          if (i0 + tid == 0) {
+            geo[tid] = make_double4(cx_b, cy_b, -ir_b, 0.0);
           } else {
-            sz[q] = make_double2(0.0, 0.0);
-            sp[q] = make_double2(0.0, 0.0);
+            const int cw = w_src[wb + i0 + tid - 1];
+            geo[tid] = make_double4(cxv[cw], cyv[cw], rad[cw], 0.0);
           }
         }
         __syncthreads();
+        for (int i = fs; i < ni; i += Sf) {
+          const double4 g4 = geo[i];
+          const double dx = zx - g4.x, dy = zy - g4.y;
+          const bool local = g4.z < 0.0;
+          // local: w = d / rad and sum_l b_l w^l; W box: rho = rad / d and
+          // sum_k a_k rho^k
+          const double i2 = rcp64(fma(dx, dx, dy * dy));
+          const cx<double> iz{dx * i2, -dy * i2};
+          const cx<double> w{local ? -g4.z * dx : g4.z * iz.x, local ? -g4.z * dy : g4.z * iz.y};
+          const cx<double> *a = co + i * P;
+          cx<double> acc = a[P - 1], dv{0.0, 0.0};
+          const double sh1 = local ? 0.0 : 1.0;
+          if constexpr (MODE == kLeafDeriv) dv = (P - 1 + sh1) * acc;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          if (c >= nch) continue;  // uniform
-          const int Sc = S[c], niter = tpad >> __builtin_ctz(Sc);
-          const double zx = zxs[c], zy = zys[c];
-          double f = fld[c];
-          const double2 *zq = sz + sl[c];
-          const double2 *pq = sp + sl[c];
-#pragma unroll 2
-          for (int it = 0; it < niter; ++it) {
-            const double2 s2 = zq[it * Sc];
-            const double2 p2 = pq[it * Sc];
-            const double dx = zx - s2.x, dy = zy - s2.y;
-            // |d|^2 + 1e-300: a target's own source (d = 0) contributes
-            // 0 * rcp(1e-300) = 0; any other |d|^2 above 1e-284 is unchanged
-            const double d2 = fma(dx, dx, fma(dy, dy, 1e-300));
-            f += fma(p2.x, dx, p2.y * dy) * rcp64(d2);
+          for (int k = P - 2; k >= 0; --k) {
+            const cx<double> c = a[k];
+            if constexpr (MODE == kLeafDeriv) {  // (no l = 0 term when local)
+              const cx<double> n = cfma(dv, w, (k + sh1) * c);
+              dv = k > 0 || !local ? n : dv;
+            }
+            acc = cfma(acc, w, c);
           }
-          fld[c] = f;
+          const cx<double> t = local ? acc : acc * w;
+          if constexpr (MODE == kLeafField) {
+            far[r] += t.x;
+          } else {
+            far[0] += t.x;
+            far[1] += t.y;
+          }
+          if constexpr (MODE == kLeafDeriv) {  // d w / d z = 1 / rad or -rho / d
+            const cx<double> d = local ? cx<double>{g4.z * dv.x, g4.z * dv.y} : (dv * w) * iz;
+            far[2] -= d.x;
+            far[3] -= d.y;
+          }
         }
         __syncthreads();
       }
     }
+    auto stage = [&](int q0, int take, int tpad) {
+      for (int q = tid; q < tpad; q += nth) {
+        const bool in = q < take;
+        const int64_t j = in ? uf_idx[uf0 + q0 + q] : 0;
+        sz[q] = in ? make_double2(sx[j], sy[j]) : make_double2(0.0, 0.0);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (c >= nch) continue;  // uniform
-      double field = fld[c];
-      for (int o = 64 >> __builtin_ctz(S[c]); o < 64; o <<= 1) field += __shfl_xor(field, o, 64);
-      if (act[c] && sl[c] == 0) {
-        const int64_t api = tperm[tb0 + ti[c]];
-        double val = scale * field;
-        if (as.sigma) {
-          const double sg = as.sigma[(int64_t)r * as.ldx + api];
-          val += (as.ident + as.tau[api]) * sg +
-                 as.gamma[r * as.G + (as.geo ? as.geo[api] : 0)];
+        for (int r = 0; r < RB; ++r) {
+          cx<double> pj{0.0, 0.0};
+          if (in && r < nr) pj = p[(int64_t)(r0 + r) * ns + j];
+          sp[q * RB + r] = make_double2(pj.x, pj.y);
         }
-        out[(int64_t)r * ldy + api] = val;
+      }
+    };
+    // value c of every lane's targets through LDS: red[slice][target], the
+    // far parts behind them; lane t < nt adds its target's parts
+    double tot[NF];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) tot[c] = 0.0;
+    auto fin = [&](int c, int sl, int tl, int tp, int S, const auto &v, auto kk) {
+      constexpr int K = decltype(kk)::value;
+      const int row = tp * K;
+      double *fr = sh + S * row;
+#pragma unroll
+      for (int k = 0; k < K; ++k) sh[sl * row + k * tp + tl] = v[k];
+      fr[tid] = far[c];
+      __syncthreads();
+      if (tid < nt) {
+        double s = 0.0;
+        for (int q = 0; q < Sf; ++q) s += fr[(q << lgf) + tid];
+        for (int q = 0; q < S; ++q) s += sh[q * row + tid];
+        tot[c] = s;
+      }
+      __syncthreads();
+    };
+    // 16 lanes a slice above 32 targets, else 8 (fewer for fewer targets)
+    const int lg = nt > 32 ? 4 : nt >= 8 ? 3 : __builtin_ctz(pow2_at_least(nt));
+    switch ((nt + (1 << lg) - 1) >> lg) {  // block-uniform
+      case 1: near_field64<MODE, RB, 1>(nt, lg, utot, stage_n, txc, tyc, sz, sp, stage, fin); break;
+      case 2: near_field64<MODE, RB, 2>(nt, lg, utot, stage_n, txc, tyc, sz, sp, stage, fin); break;
+      case 3: near_field64<MODE, RB, 3>(nt, lg, utot, stage_n, txc, tyc, sz, sp, stage, fin); break;
+      default: near_field64<MODE, RB, 4>(nt, lg, utot, stage_n, txc, tyc, sz, sp, stage, fin); break;
+    }
+    if (tid < nt) {
+      const int64_t api = tperm[tb0 + tc0 + tid];
+      if constexpr (MODE == kLeafField) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          if (r < nr) {
+            double val = scale * tot[r];
+            if (as.sigma) {
+              const double sg = as.sigma[(int64_t)(r0 + r) * as.ldx + api];
+              val += (as.ident + as.tau[api]) * sg +
+                     as.gamma[(r0 + r) * as.G + (as.geo ? as.geo[api] : 0)];
+            }
+            out[(int64_t)(r0 + r) * ldy + api] = val;
+          }
+        }
+      } else {
+        out[2 * api] = tot[0];
+        out[2 * api + 1] = tot[1];
+        if constexpr (MODE == kLeafDeriv) {
+          dout[2 * api] = tot[2];
+          dout[2 * api + 1] = tot[3];
+        }
       }
     }
   }
+}
+
+// Waves per leaf of the FP64 leaf kernel: one where the leaves alone fill
+// the chip (each wave then pays the staging and the joining once), two or
+// four below, where a leaf's own chain of loads and sums is the time.
+// Field of one right-hand side, one / two / four waves: 161 / 181 / - us at
+// 31920 leaves, 62 / 58 / - at 11164, 43 / 28 / 33 at 3351, 31 / 20 / 18 at
+// 822; the complex fields, with more work per pair, gain from a second wave
+// only below 8192 leaves (transposed application 216 / 229 us at 11164).
+static int leaf64_waves(int64_t groups, bool field) {
+  return groups >= (field ? 16384 : 8192) ? 1 : groups >= 2048 ? 2 : 4;
+}
+
+// Launch of k_leaf64 over the plan's target leaves.
+template <int P, int MODE, int RB>
+static void launch_leaf64(const DevPlan &pl, const int64_t *ufp, const int32_t *uf_idx,
+                          const double *sx, const double *sy, const cx<double> *p, int64_t ns,
+                          const cx<double> *M, const cx<double> *L, int nrhs, double *out,
+                          double *dout, int64_t ldy, double scale, const Assembly &as,
+                          hipStream_t s) {
+  if (pl.n_leaf_t == 0) return;
+  const int ry = (nrhs + RB - 1) / RB;
+  const int64_t groups = (int64_t)pl.n_leaf_t * ry;
+  const int W = leaf64_waves(groups, MODE == kLeafField);
+  const size_t stage = (size_t)kStage * std::min(W, 2) * (1 + RB) * sizeof(double2);
+  const size_t red = (size_t)(256 + 64) * W * sizeof(double);
+  const size_t fari = kFarItems * (sizeof(double4) + P * sizeof(cx<double>));
+  hipLaunchKernelGGL((k_leaf64<P, MODE, RB>), dim3(pl.n_leaf_t, ry), dim3(64 * W),
+                     std::max(std::max(stage, red), fari), s, pl.lt_hdr.p, pl.cx.p, pl.cy.p, pl.rad.p, pl.tx.p,
+                     pl.ty.p, pl.tgt_perm.p, ufp, uf_idx, pl.w_src.p, sx, sy, p, ns, M, L,
+                     pl.nbox, nrhs, out, dout, ldy, scale, as);
 }
 
 // A staged U-list source of the FP32 leaf kernel: position (FP64) and the
@@ -1563,12 +1718,14 @@ static void run64(const DevPlan &pl, const Tables &tb, Workspace &ws,
   }
   if (pl.n_leaf_t > 0) {
     TimerScope ts(ws.timer, ST_LEAF, s);
-    hipLaunchKernelGGL((k_leaf64<P>), dim3(pl.n_leaf_t, nrhs), dim3(64), 0, s,
-                       pl.lt_hdr.p, pl.cx.p, pl.cy.p, pl.rad.p,
-                       pl.tx.p, pl.ty.p, pl.tgt_perm.p, pl.uf_idx.p,
-                       pl.w_src.p, pl.sx.p, pl.sy.p,
-                       (const cx<double> *)p, pl.ns, (const cx<double> *)M,
-                       (const cx<double> *)L, pl.nbox, out, ldy, scale, as);
+    // four right-hand sides per work-group share each pair's difference and
+    // reciprocal (four columns at 1.02M nodes 417 us against 682 with a
+    // group each, 178 against 206 at 256k) where that leaves enough groups;
+    // below 8192 the groups are too few (3351: 96 us, and 70 with one each)
+    const bool four = nrhs > 1 && (int64_t)pl.n_leaf_t * ((nrhs + 3) / 4) >= 8192;
+    const auto launch = four ? launch_leaf64<P, kLeafField, 4> : launch_leaf64<P, kLeafField, 1>;
+    launch(pl, nullptr, pl.uf_idx.p, pl.sx.p, pl.sy.p, p, pl.ns, M, L, nrhs, out, nullptr, ldy,
+           scale, as, s);
   }
 }
 
@@ -1683,120 +1840,6 @@ __global__ void k_strengths_given(int64_t ns, const int64_t *__restrict__ perm,
   p[j] = cx<double>{pin[2 * a], pin[2 * a + 1]};
 }
 
-// Psi and (DERIV) Psi' at the targets of one leaf (one 64-lane block):
-// lanes are (target, slice) as in the FP32 kernels, tp = pow2 >= #targets
-// (64 above 32 targets) lanes per slice and S = 64 / tp slices, each taking
-// every S-th W-list box and staged source; slices are summed by shuffles.
-// Reciprocals by rcp64 (hardware estimate and two Newton-Raphson steps).
-template <int P, bool DERIV>
-__global__ void __launch_bounds__(64)
-    k_leaf64_full(const int32_t *__restrict__ leaves,
-                  const int32_t *__restrict__ lev,
-                  const int64_t *__restrict__ t0, const int64_t *__restrict__ t1,
-                  const int64_t *__restrict__ s0, const int64_t *__restrict__ s1,
-                  const double *__restrict__ cxv, const double *__restrict__ cyv,
-                  const double *__restrict__ rad,
-                  const double *__restrict__ tx, const double *__restrict__ ty,
-                  const int64_t *__restrict__ tperm,
-                  const int64_t *__restrict__ uf_ptr,
-                  const int32_t *__restrict__ uf_idx,
-                  const int32_t *__restrict__ w_ptr,
-                  const int32_t *__restrict__ w_src,
-                  const double *__restrict__ sx, const double *__restrict__ sy,
-                  const cx<double> *__restrict__ p,
-                  const cx<double> *__restrict__ M,
-                  const cx<double> *__restrict__ L,
-                  double *__restrict__ psi, double *__restrict__ dpsi) {
-  __shared__ double2 sz[kStage];
-  __shared__ double2 sp[kStage];
-  const int b = leaves[blockIdx.x];
-  const int lane = threadIdx.x;
-  const int64_t tb0 = t0[b], ntb = t1[b] - tb0;
-  const int tp = ntb <= 32 ? pow2_at_least((int)ntb) : 64;
-  const int S = 64 / tp, tl = lane % tp, sl = lane / tp;
-  const int64_t uf0 = uf_ptr[b];
-  const int utot = (int)(uf_ptr[b + 1] - uf0);  // U-list sources of the leaf
-  const int wb = w_ptr[b], we = w_ptr[b + 1];
-  for (int64_t tc = 0; tc < ntb; tc += tp) {
-    const int64_t i = tb0 + tc + tl;
-    const bool act = tc + tl < ntb;
-    const double zx = act ? tx[i] : 0.0, zy = act ? ty[i] : 0.0;
-    cx<double> f{0.0, 0.0}, df{0.0, 0.0};
-    if (act) {
-      if (sl == 0 && lev[b] >= 2) {
-        const double ir = 1.0 / rad[b];
-        const cx<double> w{(zx - cxv[b]) * ir, (zy - cyv[b]) * ir};
-        const cx<double> *Lb = L + (int64_t)b * P;
-        cx<double> acc = Lb[P - 1], dacc = (double)(P - 1) * Lb[P - 1];
-        for (int l = P - 2; l >= 1; --l) {
-          acc = cfma(acc, w, Lb[l]);
-          if constexpr (DERIV) dacc = dacc * w + (double)l * Lb[l];
-        }
-        acc = cfma(acc, w, Lb[0]);
-        f = f + acc;
-        if constexpr (DERIV) df = df + ir * dacc;
-      }
-      for (int e = wb + sl; e < we; e += S) {
-        const int c = w_src[e];
-        const double dx = zx - cxv[c], dy = zy - cyv[c];
-        const double r2 = rcp64(fma(dx, dx, dy * dy));
-        const cx<double> iz{dx * r2, -dy * r2};
-        const cx<double> rho = rad[c] * iz;
-        const cx<double> *a = M + (int64_t)c * P;
-        cx<double> acc = a[P - 1], dacc = (double)P * a[P - 1];
-        for (int k = P - 2; k >= 0; --k) {
-          acc = cfma(acc, rho, a[k]);
-          if constexpr (DERIV) dacc = dacc * rho + (double)(k + 1) * a[k];
-        }
-        f = f + acc * rho;
-        if constexpr (DERIV) df = df - (dacc * rho) * iz;
-      }
-    }
-    {  // the leaf's U-list sources, kStage at a time
-      const int total = utot;
-      for (int q0 = 0; q0 < total; q0 += kStage) {
-        const int take = min(kStage, total - q0);
-        for (int q = lane; q < take; q += 64) {
-          const int64_t j = uf_idx[uf0 + q0 + q];
-          sz[q] = make_double2(sx[j], sy[j]);
-          sp[q] = make_double2(p[j].x, p[j].y);
-        }
-        __syncthreads();
-        if (act) {
-          for (int q = sl; q < take; q += S) {
-            const double dx = zx - sz[q].x, dy = zy - sz[q].y;
-            // 1 / d = conj(d) / |d|^2; the bias makes a source at the
-            // target (d = 0) contribute 0
-            const double r2 = rcp64(fma(dx, dx, fma(dy, dy, 1e-300)));
-            const cx<double> iv{dx * r2, -dy * r2};
-            const cx<double> t = cx<double>{sp[q].x, sp[q].y} * iv;
-            f = f + t;
-            if constexpr (DERIV) df = df - t * iv;
-          }
-        }
-        __syncthreads();
-      }
-    }
-    for (int o = tp; o < 64; o <<= 1) {
-      f.x += __shfl_xor(f.x, o, 64);
-      f.y += __shfl_xor(f.y, o, 64);
-      if constexpr (DERIV) {
-        df.x += __shfl_xor(df.x, o, 64);
-        df.y += __shfl_xor(df.y, o, 64);
-      }
-    }
-    if (act && sl == 0) {
-      const int64_t api = tperm[i];
-      psi[2 * api] = f.x;
-      psi[2 * api + 1] = f.y;
-      if constexpr (DERIV) {
-        dpsi[2 * api] = df.x;
-        dpsi[2 * api + 1] = df.y;
-      }
-    }
-  }
-}
-
 template <int P>
 static void run64_full(const DevPlan &pl, const Tables &tb, Workspace &ws,
                        double *psi, double *dpsi, hipStream_t s) {
@@ -1804,16 +1847,9 @@ static void run64_full(const DevPlan &pl, const Tables &tb, Workspace &ws,
   auto *M = (cx<double> *)ws.mult64.p;
   auto *L = (cx<double> *)ws.loc64.p;
   far_field<double, P>(pl, tb, ws, p, M, L, 1, s);
-  if (pl.n_leaf_t > 0) {
-    auto k = dpsi ? k_leaf64_full<P, true> : k_leaf64_full<P, false>;
-    hipLaunchKernelGGL(k, dim3(pl.n_leaf_t), dim3(64), 0, s,
-                       pl.leaf_t.p, pl.lev.p, pl.t0.p, pl.t1.p, pl.s0.p,
-                       pl.s1.p, pl.cx.p, pl.cy.p, pl.rad.p, pl.tx.p, pl.ty.p,
-                       pl.tgt_perm.p, pl.uf_ptr.p, pl.uf_idx.p, pl.w_ptr.p,
-                       pl.w_src.p, pl.sx.p, pl.sy.p, (const cx<double> *)p,
-                       (const cx<double> *)M, (const cx<double> *)L, psi,
-                       dpsi);
-  }
+  const auto launch = dpsi ? launch_leaf64<P, kLeafDeriv, 1> : launch_leaf64<P, kLeafPsi, 1>;
+  launch(pl, nullptr, pl.uf_idx.p, pl.sx.p, pl.sy.p, p, pl.ns, M, L, 1, psi, dpsi, 0, 1.0,
+         Assembly{}, s);
 }
 
 void fmm_apply64_full(const DevPlan &pl, const Tables &tb, Workspace &ws,
@@ -1884,14 +1920,9 @@ static void run64_sources(const DevPlan &pl, const Tables &tb, Workspace &ws,
   run_pass<double, P, true>(pl.dn[1], (const double *)tb.bc64.p, (const cx<double> *)tb.pre64.p,
                             (const cx<double> *)tb.post64.p, L, pl.nbox, 1, s);
   // at the plan's targets: local expansions, W lists, direct sums
-  if (pl.n_leaf_t > 0) {
-    auto k = dpsi ? k_leaf64_full<P, true> : k_leaf64_full<P, false>;
-    hipLaunchKernelGGL(k, dim3(pl.n_leaf_t), dim3(64), 0, s, pl.leaf_t.p,
-                       pl.lev.p, pl.t0.p, pl.t1.p, pl.s0.p, pl.s1.p, pl.cx.p, pl.cy.p, pl.rad.p,
-                       pl.tx.p, pl.ty.p, pl.tgt_perm.p, ps.d_ptr.p, ps.d_t.p, pl.w_ptr.p,
-                       pl.w_src.p, ps.x, ps.y, pin, (const cx<double> *)M,
-                       (const cx<double> *)L, psi, dpsi);
-  }
+  const auto launch = dpsi ? launch_leaf64<P, kLeafDeriv, 1> : launch_leaf64<P, kLeafPsi, 1>;
+  launch(pl, ps.d_ptr.p, ps.d_t.p, ps.x, ps.y, pin, ps.n, M, L, 1, psi, dpsi, 0, 1.0,
+         Assembly{}, s);
 }
 
 void fmm_sources64_full(const DevPlan &pl, const Tables &tb, Workspace &ws, PointSources &ps,
