@@ -364,7 +364,8 @@ struct GmresState {
   int R = 0, S = 0, m = 0;
   int64_t n = 0;
   DBuf<double> V, H, cs, sn, gv, yv, h1, h2, nrm2, tol, resid;
-  DBuf<int32_t> active, kused, count;
+  DBuf<int32_t> active, kused, count, tally;
+  DBuf<double> part1, part2;  // partial sums of the Gram-Schmidt steps
   DBuf<double> bvec, rvec, xvec, dvec, bn2;
 };
 
@@ -436,6 +437,7 @@ struct lbs_ctx {
   Workspace ws;
   SegPlan seg_nodes;   // one segment per geometry over the node rows
   SegPlan seg_sys;     // one segment per geometry over the N + M unknowns
+  SegPlan seg_gs;      // the same in the chunks of the Gram-Schmidt steps
   std::vector<double> xi_x, xi_y;  // node images, API order (eval trees)
   StageTimer timer;
   GmresState gm;
@@ -521,14 +523,11 @@ void apply_precond_op_ws(lbs_ctx &c, Workspace &w, int prec, int nrhs, const dou
   apply_K_ws(c, w, prec, nrhs, x, n, y, n, 0.0, s);
   {
     TimerScope ts(w.timer, ST_CONSTRAINT, s);
-    launch_island_sums(g, y, n, nrhs, w.tmpM.p, g.M, s);
-    launch_gemv_blocks(g, w.tmpM.p, g.M, nrhs, y + g.N, n, -1.0, s);
+    launch_island_sums(g, y, n, nrhs, y + g.N, n, s);
+    launch_gemv_blocks(g, y + g.N, n, nrhs, w.tmpM.p, g.M, -1.0, s);
   }
-  {
-    TimerScope ts(w.timer, ST_LOGSRC, s);
-    launch_logsrc_apply(g, w, y + g.N, n, nrhs, y, n, -1.0, s);
-  }
-  launch_axpby(n * nrhs, 1.0, x, 1.0, y, s);
+  TimerScope ts(w.timer, ST_LOGSRC, s);
+  launch_logsrc_apply(g, w, w.tmpM.p, g.M, nrhs, y, n, -1.0, s, x);
 }
 
 void apply_precond_op(lbs_ctx &c, int prec, int nrhs, const double *x,
@@ -593,6 +592,10 @@ void ensure_gmres(lbs_ctx &c, int R) {
   st.active.alloc(S);
   st.kused.alloc(S);
   st.count.alloc(1);
+  st.tally.alloc(2);
+  LBS_HIP(hipMemset(st.tally.p, 0, 2 * sizeof(int32_t)));
+  st.part1.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
+  st.part2.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
   st.bvec.alloc((size_t)R * n);
   st.rvec.alloc((size_t)R * n);
   st.xvec.alloc((size_t)R * n);
@@ -620,7 +623,8 @@ std::vector<const void *> graph_signature(lbs_ctx &c) {
   const Workspace &w = c.ws;
   const AdjState &a = c.adj;
   return {st.V.p, st.H.p, st.cs.p, st.sn.p, st.gv.p, st.h1.p, st.h2.p, st.nrm2.p,
-          st.tol.p, st.resid.p, st.active.p, st.kused.p, st.count.p, w.pstr64.p,
+          st.tol.p, st.resid.p, st.active.p, st.kused.p, st.count.p, st.tally.p, st.part1.p,
+          st.part2.p, w.pstr64.p,
           w.mult64.p, w.loc64.p, w.pstr32.p, w.mult32.p, w.loc32.p, w.gam.p,
           w.gpart.p, w.gcsum.p, w.gcnt.p, w.red.p, w.tmpM.p, w.logL.p, a.mom.p, a.tA.p, a.lam.p, a.pc.p, a.Fc.p,
           a.ysum.p, c.geo.SinvT.p};
@@ -681,18 +685,17 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
       double *vk = V + (int64_t)k * ldv, *w = V + (int64_t)(k + 1) * ldv;
       auto body = [&](hipStream_t q) {
         op(vk, w, q);
-        launch_segdots(c.seg_sys, R, k + 1, V, ldv, n, w, n, st.h1.p, c.ws.red.p, q);
-        launch_maxpy_seg(n, R, G, k + 1, rg, V, ldv, st.h1.p, w, q);
-        if (passes > 1) {
-          launch_segdots(c.seg_sys, R, k + 1, V, ldv, n, w, n, st.h2.p, c.ws.red.p, q);
-          launch_maxpy_seg(n, R, G, k + 1, rg, V, ldv, st.h2.p, w, q);
-        }
-        launch_segdots(c.seg_sys, R, 1, w, 0, n, w, n, st.nrm2.p, c.ws.red.p, q);
-        launch_fill_int(1, 0, st.count.p, q);
-        launch_givens_seg(S, k, m, st.h1.p, passes > 1 ? st.h2.p : nullptr, st.nrm2.p,
-                          st.tol.p, st.H.p,
-                          st.cs.p, st.sn.p, st.gv.p, st.resid.p, st.active.p,
-                          st.kused.p, st.count.p, q);
+        launch_gs_dots(c.seg_gs, R, k + 1, V, ldv, n, w, st.part1.p, q);
+        if (passes > 1)
+          launch_gs_update(c.seg_gs, R, k + 1, V, ldv, n, w, st.part1.p, st.h1.p, true,
+                           st.part2.p, q);
+        const double *in = passes > 1 ? st.part2.p : st.part1.p;
+        double *np = passes > 1 ? st.part1.p : st.part2.p;
+        launch_gs_update(c.seg_gs, R, k + 1, V, ldv, n, w, in,
+                         passes > 1 ? st.h2.p : st.h1.p, false, np, q);
+        launch_gs_givens(c.seg_gs, S, k, m, np, st.h1.p, passes > 1 ? st.h2.p : nullptr,
+                         st.nrm2.p, st.tol.p, st.H.p, st.cs.p, st.sn.p, st.gv.p, st.resid.p,
+                         st.active.p, st.kused.p, st.tally.p, st.count.p, q);
         launch_normalize_seg(n, R, G, rg, st.nrm2.p, st.active.p, w, w, q);
       };
       if (use_graphs) {
@@ -1234,6 +1237,13 @@ std::vector<lbs_island> sampled_islands(const Samples &sm, int M,
   return isl;
 }
 
+// Rows per chunk of the Gram-Schmidt kernels: one to four rows per thread,
+// at most about 256 chunks until four rows are reached (at 77k rows 128 and
+// 256 chunks take the same 6.85 ms per solve, 512 7.13).
+int64_t gs_rows(int64_t n) {
+  return std::min<int64_t>(1024, std::max<int64_t>(256, (n / 256 + 255) / 256 * 256));
+}
+
 lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in,
                     const int32_t *nodes, const lbs_options *opt,
                     hipStream_t s, const Samples *sm = nullptr) {
@@ -1531,6 +1541,7 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
     }
     ctx->seg_nodes.build(rn, s);
     ctx->seg_sys.build(rs, s);
+    ctx->seg_gs.build(rs, s, gs_rows(N + M));
   }
   // Schur complements S = D - F E and their inverses, one block per geometry
   {

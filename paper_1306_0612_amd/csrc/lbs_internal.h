@@ -306,10 +306,12 @@ struct ClosePlan {
 // row chunks of at most 2048 rows.
 struct SegPlan {
   int nseg = 0, nchunk = 0;
+  int maxseg = 0;      // chunks of the largest segment
   DBuf<int64_t> c0, c1;
   DBuf<int32_t> sptr, sidx;
+  DBuf<int32_t> cseg;  // segment of each chunk
   void build(const std::vector<std::vector<std::pair<int64_t, int64_t>>> &ranges,
-             hipStream_t s);
+             hipStream_t s, int64_t rows = 2048);
 };
 
 struct Workspace {
@@ -469,10 +471,11 @@ void launch_segdots(const SegPlan &sp, int R, int nvec, const double *a,
                     double *out, double *scratch, hipStream_t s);
 
 // log sources and constraint rows (solver.hip)
-// out += alpha E z
+// out += alpha E z; with add (columns like out, of length N + M) also
+// out += add on the node rows and out = add + z on the island rows
 void launch_logsrc_apply(const Geometry &g, Workspace &ws, const double *z,
                          int64_t ldz, int nrhs, double *out, int64_t ldo,
-                         double alpha, hipStream_t s);
+                         double alpha, hipStream_t s, const double *add = nullptr);
 void launch_logsrc_local(const Geometry &g, Workspace &ws, const double *z,
                          hipStream_t s);
 void launch_island_sums(const Geometry &g, const double *y, int64_t ldy,
@@ -504,9 +507,14 @@ void launch_eval_logsrc(const Geometry &g, int64_t T, const double *txyz,
                         hipStream_t s, DBuf<double> *scratch = nullptr);
 
 // GMRES building blocks (solver.hip)
-void launch_maxpy_seg(int64_t n, int R, int G, int k1, const int32_t *row_geo,
-                      const double *V, int64_t ldv, const double *h, double *w,
-                      hipStream_t s);
+// part: partial sums of V^T w (k1 columns)
+void launch_gs_dots(const SegPlan &sp, int R, int k1, const double *V, int64_t ldv, int64_t ldc,
+                    const double *w, double *part, hipStream_t s);
+// w -= V h, h (also to hout) from the partial sums `in`; part: the partial
+// sums of V^T w (dots) or of |w|^2
+void launch_gs_update(const SegPlan &sp, int R, int k1, const double *V, int64_t ldv,
+                      int64_t ldc, double *w, const double *in, double *hout, bool dots,
+                      double *part, hipStream_t s);
 void launch_update_seg(int64_t n, int R, int G, int k, int m,
                        const int32_t *row_geo, const double *V, int64_t ldv,
                        const double *y, double *x, hipStream_t s);
@@ -516,11 +524,11 @@ void launch_normalize_seg(int64_t n, int R, int G, const int32_t *row_geo,
 void launch_gmres_start(int S, int m, const double *nrm2, const double *tol,
                         double *g, int32_t *active, int32_t *kused,
                         int32_t *count, hipStream_t s);
-void launch_givens_seg(int S, int k, int m, const double *h1, const double *h2,
-                       const double *nrm2, const double *tol, double *H,
-                       double *cs, double *sn, double *g, double *resid,
-                       int32_t *active, int32_t *kused, int32_t *count,
-                       hipStream_t s);
+void launch_gs_givens(const SegPlan &sp, int S, int k, int m, const double *npart,
+                      const double *h1, const double *h2, double *nrm2, const double *tol,
+                      double *H, double *cs, double *sn, double *g, double *resid,
+                      int32_t *active, int32_t *kused, int32_t *tally, int32_t *count,
+                      hipStream_t s);
 void launch_backsolve_seg(int S, int m, const double *H, const double *g,
                           const int32_t *kused, double *y, hipStream_t s);
 void launch_axpby(int64_t n, double a, const double *x, double b, double *y,

@@ -189,7 +189,8 @@ __global__ void __launch_bounds__(256)
                   const int32_t *__restrict__ near_idx,
                   const double *__restrict__ z, int64_t ldz,
                   const double *__restrict__ Lc,
-                  double *__restrict__ out, int64_t ldo, double alpha) {
+                  double *__restrict__ out, int64_t ldo, double alpha,
+                  const double *__restrict__ add) {
   constexpr int P = kPlog, stride = log_stride<P>();
   const int k = blockIdx.x, r = blockIdx.y;
   const double *L = Lc + ((int64_t)r * M + k) * stride;
@@ -211,7 +212,12 @@ __global__ void __launch_bounds__(256)
       tot += zr[m] * 0.5 * log(d0 * d0 + d1 * d1 + d2 * d2);
     }
     const double ez = -kInvPi * tot + kLog2 * 0.5 * kInvPi * L[2 * (P + 1) + 1];
-    out[(int64_t)r * ldo + i] += alpha * ez;
+    const double o = out[(int64_t)r * ldo + i] + alpha * ez;
+    out[(int64_t)r * ldo + i] = add ? add[(int64_t)r * ldo + i] + o : o;
+  }
+  if (add && threadIdx.x == 0) {  // the island's own row, behind the node rows
+    const int64_t i = (int64_t)r * ldo + offs[M] + k;
+    out[i] = add[i] + zr[k];
   }
 }
 
@@ -297,7 +303,7 @@ void launch_logsrc_local(const Geometry &g, Workspace &ws, const double *z,
 
 void launch_logsrc_apply(const Geometry &g, Workspace &ws, const double *z,
                          int64_t ldz, int nrhs, double *out, int64_t ldo,
-                         double alpha, hipStream_t s) {
+                         double alpha, hipStream_t s, const double *add) {
   if (g.M == 0 || g.N == 0) return;
   hipLaunchKernelGGL(k_logsrc_local, dim3(g.M, nrhs, 2), dim3(64), 0, s, g.M,
                      g.isl_geo.p, g.dgisl.p, g.far_ptr.p, g.far_cptr.p,
@@ -306,7 +312,7 @@ void launch_logsrc_apply(const Geometry &g, Workspace &ws, const double *z,
   hipLaunchKernelGGL(k_logsrc_node, dim3(g.M, nrhs), dim3(256), 0, s, g.M,
                      g.doffs.p, g.xil.p, g.xyz.p, g.elll.p, g.rhol.p,
                      g.dcenter.p, g.nearR_ptr.p, g.nearR_idx.p, z, ldz,
-                     ws.logL.p, out, ldo, alpha);
+                     ws.logL.p, out, ldo, alpha, add);
   LBS_HIP(hipGetLastError());
 }
 
@@ -1322,24 +1328,28 @@ __global__ void __launch_bounds__(256)
 }
 
 void SegPlan::build(const std::vector<std::vector<std::pair<int64_t, int64_t>>> &ranges,
-                    hipStream_t s) {
+                    hipStream_t s, int64_t rows) {
   std::vector<int64_t> a0, a1;
-  std::vector<int32_t> ptr(1, 0), idx;
+  std::vector<int32_t> ptr(1, 0), idx, seg;
   nseg = (int)ranges.size();
   for (int g = 0; g < nseg; ++g) {
     for (auto &rg : ranges[g])
-      for (int64_t x = rg.first; x < rg.second; x += kChunkRows) {
+      for (int64_t x = rg.first; x < rg.second; x += rows) {
         idx.push_back((int32_t)a0.size());
+        seg.push_back(g);
         a0.push_back(x);
-        a1.push_back(std::min<int64_t>(rg.second, x + kChunkRows));
+        a1.push_back(std::min<int64_t>(rg.second, x + rows));
       }
     ptr.push_back((int32_t)idx.size());
   }
   nchunk = (int)a0.size();
+  maxseg = 0;
+  for (int g = 0; g < nseg; ++g) maxseg = std::max(maxseg, ptr[g + 1] - ptr[g]);
   c0.upload(a0, s);
   c1.upload(a1, s);
   sptr.upload(ptr, s);
   sidx.upload(idx, s);
+  cseg.upload(seg, s);
 }
 
 void launch_segdots(const SegPlan &sp, int R, int nvec, const double *a,
@@ -1362,31 +1372,6 @@ void launch_segdots(const SegPlan &sp, int R, int nvec, const double *a,
 // all geometries; row_geo gives each row's geometry.  Per-system state:
 // H[s][(m+1) m] (column-major per system), cs, sn, g (m+1), y, residual,
 // tolerance, active flag and the number of Arnoldi columns in use.
-
-// w[r][i] -= sum_{j < k1} h[j S + s] V_j[r][i]
-__global__ void k_maxpy_seg(int64_t n, int R, int G, int k1,
-                            const int32_t *__restrict__ row_geo,
-                            const double *__restrict__ V, int64_t ldv,
-                            const double *__restrict__ h,
-                            double *__restrict__ w) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (i >= n) return;
-  const int S = R * G;
-  const int s = r * G + row_geo[i];
-  const int64_t off = (int64_t)r * n + i;
-  double acc = 0.0;
-  for (int j = 0; j < k1; ++j) acc += h[j * S + s] * V[(int64_t)j * ldv + off];
-  w[off] -= acc;
-}
-
-void launch_maxpy_seg(int64_t n, int R, int G, int k1, const int32_t *row_geo,
-                      const double *V, int64_t ldv, const double *h, double *w,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_maxpy_seg, dim3((unsigned)((n + 255) / 256), R),
-                     dim3(256), 0, s, n, R, G, k1, row_geo, V, ldv, h, w);
-  LBS_HIP(hipGetLastError());
-}
 
 // x[r][i] += sum_{j < k} y[s][j] V_j[r][i]   (y zero beyond each system's k)
 __global__ void k_update_seg(int64_t n, int R, int G, int k, int m,
@@ -1462,59 +1447,323 @@ void launch_gmres_start(int S, int m, const double *nrm2, const double *tol,
   LBS_HIP(hipGetLastError());
 }
 
-// Arnoldi step k for every active system: column k of H from the two CGS
-// passes (h1 + h2) and the norm, previous rotations, new rotation, g
-// update, residual, convergence flag; counts systems still active.
-__global__ void k_givens_seg(int S, int k, int m, const double *__restrict__ h1,
-                             const double *__restrict__ h2,
-                             const double *__restrict__ nrm2,
-                             const double *__restrict__ tol,
-                             double *__restrict__ H, double *__restrict__ cs,
-                             double *__restrict__ sn, double *__restrict__ g,
-                             double *__restrict__ resid,
-                             int32_t *__restrict__ active,
-                             int32_t *__restrict__ kused,
-                             int32_t *__restrict__ count) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S || !active[s]) return;
-  double *h = H + (int64_t)s * (m + 1) * m + (int64_t)k * (m + 1);
-  double *c = cs + (int64_t)s * m, *sg = sn + (int64_t)s * m;
-  double *gg = g + (int64_t)s * (m + 1);
-  for (int j = 0; j <= k; ++j) h[j] = h1[j * S + s] + (h2 ? h2[j * S + s] : 0.0);
-  h[k + 1] = sqrt(fmax(nrm2[s], 0.0));
-  for (int j = 0; j < k; ++j) {
-    const double t = c[j] * h[j] + sg[j] * h[j + 1];
-    h[j + 1] = -sg[j] * h[j] + c[j] * h[j + 1];
-    h[j] = t;
+// ------------------------------------------------ Gram-Schmidt of one step
+// One Arnoldi step orthogonalizes w against V_0 .. V_k (per system) in
+// three or four launches of these kernels, over row chunks that lie in one
+// segment (geometry) each; while a segment has few chunks a work-group adds
+// all their partial sums itself:
+//   k_gs_dots      partial sums of h1 = V^T w
+//   k_gs_update    w -= V h1, and (two passes) the partial sums of
+//                  h2 = V^T w with the entries of V still in registers
+//   k_gs_update    w -= V h2 and the partial sums of |w|^2
+//   k_gs_givens    the norm, the new column of H and its rotation
+// Partial sums: part[(j R + r) nchunk + c]; the chunks of a segment are
+// numbered in a row, sptr[g] .. sptr[g + 1].  Bound by reading V (8 B per
+// entry and pass) at large sizes and by launch latency at small ones; the
+// separate reduction, update, norm and fill launches that this replaces
+// took 68 us of a 240 us iteration at 77k unknowns.
+constexpr int kGsThreads = 256;
+constexpr int kGsFold = 256;  // chunks of a segment that every work-group adds itself
+
+// The total of 8 values over the 64 lanes by recursive halving: lane i
+// returns that of value i / 8.
+__device__ __forceinline__ double sum8(double (&v)[8], int lane) {
+#pragma unroll
+  for (int h = 4; h >= 1; h >>= 1) {
+    const int o = 8 * h;
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k < h) {
+        const double send = up ? v[k] : v[k + h];
+        const double keep = up ? v[k + h] : v[k];
+        v[k] = keep + __shfl_xor(send, o, 64);
+      }
+    }
   }
-  const double a = h[k], b = h[k + 1];
-  const double den = hypot(a, b);
-  double cc = 1.0, ss = 0.0;
-  if (den > 0.0) {
-    cc = a / den;
-    ss = b / den;
-  }
-  c[k] = cc;
-  sg[k] = ss;
-  h[k] = den;
-  h[k + 1] = 0.0;
-  gg[k + 1] = -ss * gg[k];
-  gg[k] = cc * gg[k];
-  const double res = fabs(gg[k + 1]);
-  resid[s] = res;
-  kused[s] = k + 1;
-  if (res <= tol[s] || !(res == res)) active[s] = 0;
-  else atomicAdd(count, 1);
+  for (int o = 4; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+  return v[0];
 }
 
-void launch_givens_seg(int S, int k, int m, const double *h1, const double *h2,
-                       const double *nrm2, const double *tol, double *H,
-                       double *cs, double *sn, double *g, double *resid,
-                       int32_t *active, int32_t *kused, int32_t *count,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_givens_seg, dim3((S + 63) / 64), dim3(64), 0, s, S, k,
-                     m, h1, h2, nrm2, tol, H, cs, sn, g, resid, active, kused,
-                     count);
+// The sum of x[a .. b) over `width` lanes of a wave (lane: index among
+// them), eight loads in flight per lane; every lane gets it.
+__device__ __forceinline__ double lane_sum(const double *__restrict__ x, int a, int b, int lane,
+                                           int width) {
+  double s = 0.0;
+  for (int e0 = a + lane; e0 < b; e0 += 8 * width) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[min(e0 + width * u, b - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += e0 + width * u < b ? v[u] : 0.0;
+  }
+  for (int o = width >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  return s;
+}
+
+// h[j S + s] from the partial sums, one wave per value.
+__global__ void __launch_bounds__(256)
+    k_gs_reduce(int nout, int nseg, int nchunk, const int32_t *__restrict__ sptr,
+                const double *__restrict__ part, double *__restrict__ h) {
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (t >= nout) return;
+  const int g = t % nseg;
+  const double s = lane_sum(part + (int64_t)(t / nseg) * nchunk, sptr[g], sptr[g + 1], lane, 64);
+  if (lane == 0) h[t] = s;
+}
+
+// Columns 8 blockIdx.z .. + 7 of V^T w over chunk blockIdx.x, right-hand
+// side blockIdx.y: a row of w is read once for eight columns.
+__global__ void __launch_bounds__(kGsThreads)
+    k_gs_dots(const int64_t *__restrict__ c0, const int64_t *__restrict__ c1, int nchunk,
+              int k1, const double *__restrict__ V, int64_t ldv, int64_t ldc,
+              const double *__restrict__ w, double *__restrict__ part) {
+  __shared__ double red[kGsThreads / 64][8];
+  const int c = blockIdx.x, r = blockIdx.y, R = gridDim.y, j0 = 8 * blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // rows relative to the chunk, so that a column's base is uniform
+  const int64_t off = (int64_t)r * ldc + c0[c];
+  const unsigned nrow = (unsigned)(c1[c] - c0[c]);
+  const double *Vc = V + off, *wc = w + off;
+  double acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.0;
+#pragma unroll 2
+  for (unsigned i = tid; i < nrow; i += kGsThreads) {
+    const double x = wc[i];
+    double v[8];  // columns past the last repeat it: all loads in flight at once
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = (Vc + (int64_t)min(j0 + j, k1 - 1) * ldv)[i];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] += v[j] * x;
+  }
+  const double t = sum8(acc, lane);
+  if ((lane & 7) == 0) red[tid >> 6][lane >> 3] = t;
+  __syncthreads();
+  if (tid < 8 && j0 + tid < k1)
+    part[((int64_t)(j0 + tid) * R + r) * nchunk + c] =
+        (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+}
+
+enum GsNext { kGsNone = 0, kGsDots = 1, kGsNorm = 2 };
+
+// w -= V h over one chunk (k1 columns), h from the partial sums `in` of the
+// chunk's segment (every work-group adds them, in the same order; the first
+// of the segment stores them to hout[j S + s]), or from hout when they are
+// added already (`in` null); then the partial sums of
+// V^T w (kGsDots, KMAX >= k1 columns held in registers) or |w|^2 (kGsNorm)
+// into `part`.
+template <int KMAX, int NEXT>
+__global__ void __launch_bounds__(kGsThreads)
+    k_gs_update(const int64_t *__restrict__ c0, const int64_t *__restrict__ c1,
+                const int32_t *__restrict__ cseg, const int32_t *__restrict__ sptr,
+                int nchunk, int nseg, int k1,
+                const double *__restrict__ V, int64_t ldv, int64_t ldc, double *__restrict__ w,
+                const double *__restrict__ in, double *__restrict__ hout,
+                double *__restrict__ part) {
+  constexpr int NT = kGsThreads, NW = NT / 64;
+  __shared__ double hs[128];
+  const int c = blockIdx.x, r = blockIdx.y, R = gridDim.y, tid = threadIdx.x, lane = tid & 63;
+  const int g = cseg[c], a = sptr[g], b = sptr[g + 1];
+  if (in) {  // sixteen lanes per column
+    for (int j = tid >> 4; j < k1; j += NT / 16) {
+      const double s = lane_sum(in + ((int64_t)j * R + r) * nchunk, a, b, tid & 15, 16);
+      if ((tid & 15) == 0) {
+        hs[j] = s;
+        if (a == c) hout[((int64_t)j * R + r) * nseg + g] = s;
+      }
+    }
+  } else if (tid < k1) {
+    hs[tid] = hout[((int64_t)tid * R + r) * nseg + g];
+  }
+  if (tid >= k1 && tid < 128) hs[tid] = 0.0;  // the repeated columns below
+  __syncthreads();
+  const int64_t off = (int64_t)r * ldc + c0[c];
+  const unsigned nrow = (unsigned)(c1[c] - c0[c]);
+  const double *Vc = V + off;
+  double *wc = w + off;
+  double nrm = 0.0;
+  if constexpr (NEXT == kGsDots) {
+    static_assert(KMAX % 8 == 0, "whole groups of eight columns");
+    double acc[KMAX];
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) acc[j] = 0.0;
+    for (unsigned i = tid; i < nrow; i += NT) {
+      double v[KMAX], s = 0.0;
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) v[j] = (Vc + (int64_t)min(j, k1 - 1) * ldv)[i];
+      const double x = wc[i];
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) s += hs[j] * v[j];
+      const double y = x - s;
+      wc[i] = y;
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) acc[j] += v[j] * y;
+    }
+    __shared__ double red[NW][KMAX];
+#pragma unroll
+    for (int j = 0; j < KMAX; j += 8) {
+      double v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = acc[j + q];
+      const double t = sum8(v, lane);
+      if ((lane & 7) == 0) red[tid >> 6][j + (lane >> 3)] = t;
+    }
+    __syncthreads();
+    if (tid < k1)
+      part[((int64_t)tid * R + r) * nchunk + c] =
+          (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  } else {
+    for (unsigned i = tid; i < nrow; i += NT) {
+      const double x = wc[i];
+      double s = 0.0;
+      for (int j0 = 0; j0 < k1; j0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = (Vc + (int64_t)min(j0 + j, k1 - 1) * ldv)[i];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += hs[j0 + j] * v[j];
+      }
+      const double y = x - s;
+      wc[i] = y;
+      nrm += y * y;
+    }
+    if constexpr (NEXT == kGsNorm) {
+      __shared__ double red[NW];
+      nrm = wave_sum(nrm);
+      if (lane == 0) red[tid >> 6] = nrm;
+      __syncthreads();
+      if (tid == 0) part[(int64_t)r * nchunk + c] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+  }
+}
+
+void launch_gs_dots(const SegPlan &sp, int R, int k1, const double *V, int64_t ldv, int64_t ldc,
+                    const double *w, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_gs_dots, dim3(sp.nchunk, R, (k1 + 7) / 8), dim3(kGsThreads), 0, s,
+                     sp.c0.p, sp.c1.p, sp.nchunk, k1, V, ldv, ldc, w, part);
+  LBS_HIP(hipGetLastError());
+}
+
+void launch_gs_update(const SegPlan &sp, int R, int k1, const double *V, int64_t ldv,
+                      int64_t ldc, double *w, const double *in, double *hout, bool dots,
+                      double *part, hipStream_t s) {
+  // a segment of many chunks: its partial sums added once, by a launch of
+  // their own
+  if (sp.maxseg > kGsFold) {
+    const int no = k1 * R * sp.nseg;
+    hipLaunchKernelGGL(k_gs_reduce, dim3((no + 3) / 4), dim3(256), 0, s, no, sp.nseg, sp.nchunk,
+                       sp.sptr.p, in, hout);
+    in = nullptr;
+  }
+  auto run = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(sp.nchunk, R), dim3(kGsThreads), 0, s, sp.c0.p, sp.c1.p,
+                       sp.cseg.p, sp.sptr.p, sp.nchunk, sp.nseg, k1, V, ldv, ldc, w, in, hout, part);
+  };
+  if (!dots) run(k_gs_update<0, kGsNorm>);
+  else if (k1 <= 16) run(k_gs_update<16, kGsDots>);
+  else if (k1 <= 32) run(k_gs_update<32, kGsDots>);
+  else if (k1 <= 56) run(k_gs_update<56, kGsDots>);
+  else {  // more columns than registers hold (restart above 56): V read again
+    run(k_gs_update<0, kGsNone>);
+    launch_gs_dots(sp, R, k1, V, ldv, ldc, w, part, s);
+  }
+  LBS_HIP(hipGetLastError());
+}
+
+// Arnoldi step k for every active system, one wave per system: the norm of
+// w from its partial sums, column k of H from the Gram-Schmidt passes
+// (h1 + h2) and the norm, previous rotations, new rotation, g update,
+// residual, convergence flag.  The last work-group to finish publishes the
+// number of systems still active and clears the counters (tally: running
+// count, finished work-groups).
+__global__ void __launch_bounds__(256)
+    k_gs_givens(int S, int G, int k, int m, int nchunk, const int32_t *__restrict__ sptr,
+                const double *__restrict__ npart, const double *__restrict__ h1, const double *__restrict__ h2,
+                double *__restrict__ nrm2, const double *__restrict__ tol,
+                double *__restrict__ H, double *__restrict__ cs, double *__restrict__ sn,
+                double *__restrict__ gv, double *__restrict__ resid,
+                int32_t *__restrict__ active, int32_t *__restrict__ kused,
+                int32_t *__restrict__ tally, int32_t *__restrict__ count) {
+  __shared__ double sh[4][128], sc[4][128], ss[4][128];
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int s = blockIdx.x * 4 + wv;
+  bool on = false;
+  if (s < S && active[s]) {
+    const int r = s / G, g = s % G;
+    const double q = lane_sum(npart + (int64_t)r * nchunk, sptr[g], sptr[g + 1], lane, 64);
+    double *c = cs + (int64_t)s * m, *sg = sn + (int64_t)s * m;
+    for (int j = lane; j <= k; j += 64) {
+      sh[wv][j] = h1[(int64_t)j * S + s] + (h2 ? h2[(int64_t)j * S + s] : 0.0);
+      if (j < k) {
+        sc[wv][j] = c[j];
+        ss[wv][j] = sg[j];
+      }
+    }
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    // every lane runs the recurrence (the same values), lane 0 stores
+    double h = sh[wv][0];
+    for (int j = 0; j < k; ++j) {
+      const double hn = sh[wv][j + 1], cj = sc[wv][j], sj = ss[wv][j];
+      const double t = cj * h + sj * hn;
+      h = -sj * h + cj * hn;
+      if (lane == 0) sh[wv][j] = t;
+    }
+    const double b = sqrt(fmax(q, 0.0)), den = hypot(h, b);
+    double cc = 1.0, sk = 0.0;
+    if (den > 0.0) {
+      cc = h / den;
+      sk = b / den;
+    }
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    double *hc = H + (int64_t)s * (m + 1) * m + (int64_t)k * (m + 1);
+    for (int j = lane; j < k; j += 64) hc[j] = sh[wv][j];
+    double *gg = gv + (int64_t)s * (m + 1);
+    const double gk = gg[k], res = fabs(sk * gk);
+    on = !(res <= tol[s] || !(res == res));
+    if (lane == 0) {
+      hc[k] = den;
+      hc[k + 1] = 0.0;
+      c[k] = cc;
+      sg[k] = sk;
+      gg[k + 1] = -sk * gk;
+      gg[k] = cc * gk;
+      nrm2[s] = q;
+      resid[s] = res;
+      kused[s] = k + 1;
+      if (!on) active[s] = 0;
+    }
+  }
+  __shared__ int32_t alive;
+  if (threadIdx.x == 0) alive = 0;
+  __syncthreads();
+  if (lane == 0 && on) atomicAdd(&alive, 1);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (gridDim.x == 1) {
+      *count = alive;
+      return;
+    }
+    if (alive) atomicAdd(&tally[0], alive);
+    __threadfence();
+    if (atomicAdd(&tally[1], 1) == (int)gridDim.x - 1) {
+      __threadfence();
+      *count = atomicExch(&tally[0], 0);
+      tally[1] = 0;
+    }
+  }
+}
+
+void launch_gs_givens(const SegPlan &sp, int S, int k, int m, const double *npart,
+                      const double *h1, const double *h2, double *nrm2, const double *tol,
+                      double *H, double *cs, double *sn, double *g, double *resid,
+                      int32_t *active, int32_t *kused, int32_t *tally, int32_t *count,
+                      hipStream_t s) {
+  hipLaunchKernelGGL(k_gs_givens, dim3((S + 3) / 4), dim3(256), 0, s, S, sp.nseg, k, m,
+                     sp.nchunk, sp.sptr.p, npart, h1, h2, nrm2, tol, H, cs, sn, g,
+                     resid, active, kused, tally, count);
   LBS_HIP(hipGetLastError());
 }
 
