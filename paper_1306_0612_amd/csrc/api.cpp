@@ -252,6 +252,41 @@ void upload_plan(Tree &T, const double *sx, const double *sy,
     LBS_HIP(hipStreamSynchronize(s));  // rng, geo are released on return
   }
   pl.m2l_box.upload(m2l, s);
+  {
+    HostPhase ph("upload_plan M2L groups");
+    // FP64 kernel: consecutive boxes in groups of at most kM2LEnt entries
+    const int n = pl.n_m2l;
+    std::vector<int32_t> gp;
+    int64_t ne = 0;
+    int first = 0;
+    for (int i = 0; i <= n; ++i) {
+      const int64_t nv = i < n ? T.v_ptr[m2l[i] + 1] - T.v_ptr[m2l[i]] : 0;
+      if (nv > 27) fail(LBS_ERR_UNSUPPORTED, "V list of more than 27 boxes");
+      if (i > first && (i == n || ne + nv > kM2LEnt || i - first == kM2LBoxes)) {
+        gp.push_back(first);
+        gp.push_back(i - first);
+        first = i;
+        ne = 0;
+      }
+      ne += nv;
+    }
+    build_m2l_groups(pl, gp, s);
+    // boxes with X lists, most sources first (by octave)
+    std::vector<std::pair<int, int32_t>> xb;
+    for (int b = 0; b < nb; ++b) {
+      int64_t nx = 0;
+      for (int e = T.x_ptr[b]; e < T.x_ptr[b + 1]; ++e) nx += T.s1[T.x_src[e]] - T.s0[T.x_src[e]];
+      int oct = 0;
+      for (int64_t v = nx; v > 1; v >>= 1) ++oct;
+      if (nx > 0) xb.push_back({-oct, b});
+    }
+    std::stable_sort(xb.begin(), xb.end(),
+                     [](const auto &a, const auto &c) { return a.first < c.first; });
+    std::vector<int32_t> xl;
+    for (const auto &x : xb) xl.push_back(x.second);
+    pl.x_box.upload(xl, s);
+    LBS_HIP(hipStreamSynchronize(s));  // xl is released on return
+  }
   auto points = [&](const std::vector<int64_t> &perm, const double *ax,
                     const double *ay, DBuf<double> &dx, DBuf<double> &dy) {
     const int64_t n = (int64_t)perm.size();

@@ -523,17 +523,19 @@ __device__ __forceinline__ void gamma_chunk(int c, int g, int r, int nch,
                                             double *__restrict__ csum,
                                             int32_t *__restrict__ cnt,
                                             double *__restrict__ gamma) {
-  __shared__ double red[4];
+  __shared__ double red[8];
   __shared__ bool last;
-  const int tid = threadIdx.x, slot = r * G + g;
+  const int tid = threadIdx.x, nth = blockDim.x, slot = r * G + g;  // 64 .. 512 threads
   const int a = gl_ptr[g] + c * kGammaChunk, b = min(gl_ptr[g + 1], a + kGammaChunk);
   double v = 0.0;
-  for (int e = a + tid; e < b; e += 256) v += gpart[(int64_t)r * nls + e];
+  for (int e = a + tid; e < b; e += nth) v += gpart[(int64_t)r * nls + e];
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if (tid < 8) red[tid] = 0.0;
+  __syncthreads();
   if ((tid & 63) == 0) red[tid >> 6] = v;
   __syncthreads();
   if (tid == 0) {
-    csum[(int64_t)slot * nch + c] = red[0] + red[1] + red[2] + red[3];
+    csum[(int64_t)slot * nch + c] = red[0] + red[1] + red[2] + red[3] + red[4] + red[5] + red[6] + red[7];
     __threadfence();
     last = atomicAdd(&cnt[slot], 1) == nch - 1;
   }
@@ -569,6 +571,127 @@ struct GammaGroups {
   double *gamma = nullptr;
   int nls = 0, G = 0, nchunk = 0, first = 0;
 };
+
+// 1 / d in FP64: the hardware estimate (2^-22 or better) and one cubic
+// correction, r (1 + e + e^2) with e = 1 - d r, which leaves e^3 < 2^-64:
+// three fused multiply-adds where two Newton-Raphson steps take four.
+__device__ __forceinline__ double rcp64(double d) {
+  const double r = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// Set-up of the FP64 M2L: each group's list entries as (source box, offset
+// code), kM2LEnt per group
+// (source -1 past the last), and its boxes as (box, number of entries up to
+// and with it | box has an X list << 16), kM2LBoxes per group (box -1 past
+// the last).  One wave per group.
+__global__ void __launch_bounds__(64)
+    k_m2l_pack(const int2 *__restrict__ grp, const int32_t *__restrict__ boxes,
+               const int32_t *__restrict__ v_ptr, const int32_t *__restrict__ v_src,
+               const uint8_t *__restrict__ v_code, const int64_t *__restrict__ xf_ptr,
+               int2 *__restrict__ ent, int2 *__restrict__ box) {
+  const int gi = blockIdx.x, lane = threadIdx.x;
+  const int2 gr = grp[gi];
+  int n = 0;
+  int2 mine = make_int2(-1, 0);
+  for (int i = 0; i < gr.y; ++i) {
+    const int b = boxes[gr.x + i], v0 = v_ptr[b], len = v_ptr[b + 1] - v0;
+    if (lane >= n && lane < n + len)
+      mine = make_int2(v_src[v0 + lane - n], (int)v_code[v0 + lane - n]);
+    n += len;
+    const int hx = xf_ptr[b + 1] > xf_ptr[b];
+    if (lane == 0) box[gi * kM2LBoxes + i] = make_int2(b, n | (hx << 16));
+  }
+  if (lane >= gr.y && lane < kM2LBoxes) box[gi * kM2LBoxes + lane] = make_int2(-1, n);
+  if (lane < kM2LEnt) ent[(int64_t)gi * kM2LEnt + lane] = mine;
+}
+
+void build_m2l_groups(DevPlan &pl, const std::vector<int32_t> &grp, hipStream_t s) {
+  pl.n_grp = (int)(grp.size() / 2);
+  if (pl.n_grp == 0) return;
+  DBuf<int32_t> dg;
+  dg.upload(grp, s);
+  pl.grp_ent.alloc((size_t)pl.n_grp * kM2LEnt);
+  pl.grp_box.alloc((size_t)pl.n_grp * kM2LBoxes);
+  hipLaunchKernelGGL(k_m2l_pack, dim3(pl.n_grp), dim3(64), 0, s,
+                     reinterpret_cast<const int2 *>(dg.p), pl.m2l_box.p, pl.v_ptr.p, pl.v_src.p,
+                     pl.v_code.p, pl.xf_ptr.p, pl.grp_ent.p, pl.grp_box.p);
+  LBS_HIP(hipGetLastError());
+  LBS_HIP(hipStreamSynchronize(s));  // dg is released on return
+}
+
+// P2L sums of two boxes with X lists per wave (entries 2 e and 2 e + 1 of
+// xbox on lanes 0-31 and 32-63), stored to L: KB coefficients in registers
+// per pass over a box's sources, one halving sum per pass inside each half;
+// a source's index is read two steps and its data one step ahead.
+struct XBoxes {
+  int n = 0;                             // boxes with X lists
+  const int32_t *box = nullptr;
+  const int64_t *xf_ptr = nullptr;
+  const int32_t *xf_idx = nullptr;
+  const double *cx = nullptr, *cy = nullptr, *rad = nullptr, *sx = nullptr, *sy = nullptr;
+  int64_t ns = 0;
+};
+
+template <int P, int KB>
+__device__ __forceinline__ void p2l_pair64(int e, int r, const XBoxes &xb,
+                                           const cx<double> *__restrict__ p,
+                                           cx<double> *__restrict__ L, int nbox) {
+  constexpr int NV = 2 * KB;
+  static_assert(NV == 32 || NV == 64, "one or two values per lane of a half");
+  const int lane = threadIdx.x & 63, hl = lane & 31;
+  const int i = 2 * e + (lane >> 5);
+  const bool has = i < xb.n;
+  const int b = xb.box[has ? i : xb.n - 1];
+  const int64_t x0 = xb.xf_ptr[b];
+  const int nx = (int)(xb.xf_ptr[b + 1] - x0);
+  const double cxb = xb.cx[b], cyb = xb.cy[b], rb = xb.rad[b];
+  const cx<double> *pr = p + (int64_t)r * xb.ns;
+  const int32_t *xi = xb.xf_idx + x0;
+  double *o = reinterpret_cast<double *>(L + ((int64_t)r * nbox + b) * P);
+  const int ql = nx - 1, steps = (nx + 31) >> 5;
+  for (int k0 = 0; k0 < P; k0 += KB) {
+    double acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+    // past the end the last source again, with strength 0
+    int jn = xi[min(hl + 32, ql)];
+    const int j0 = xi[min(hl, ql)];
+    double zx = xb.sx[j0], zy = xb.sy[j0];
+    cx<double> pj = pr[j0];
+    if (hl > ql) pj = cx<double>{0.0, 0.0};
+    for (int st = 0; st < steps; ++st) {
+      const int q1 = hl + 32 * (st + 1);
+      const double nzx = xb.sx[jn], nzy = xb.sy[jn];
+      cx<double> npj = pr[jn];
+      jn = xi[min(q1 + 32, ql)];
+      if (q1 > ql) npj = cx<double>{0.0, 0.0};
+      const double ux = zx - cxb, uy = zy - cyb;
+      const double d = rcp64(fma(ux, ux, uy * uy));
+      const cx<double> iu{ux * d, -uy * d};
+      const cx<double> rho = rb * iu;
+      cx<double> t = pj * iu;
+      t = cx<double>{-t.x, -t.y};
+      if (k0 > 0) t = t * cpow(rho, k0);
+#pragma unroll
+      for (int l = 0; l < KB; ++l) {
+        acc[2 * l] += t.x;
+        acc[2 * l + 1] += t.y;
+        t = t * rho;
+      }
+      zx = nzx;
+      zy = nzy;
+      pj = npj;
+    }
+    halving_steps_half<double, NV>(acc, lane);
+#pragma unroll
+    for (int c = 0; c < NV / 32; ++c) {  // lane hl of a half: values hl NV / 32 ..
+      const int x = 2 * k0 + hl * (NV / 32) + c;
+      if (has && x < 2 * P) o[x] = acc[c];
+    }
+  }
+}
 
 // ------------------------------------------------ upward / downward passes
 template <typename T>
@@ -607,15 +730,24 @@ __device__ __forceinline__ void scale_chunk(typename Chunk16<T>::type &v, const 
 //             post[q_child] to each child of the component
 // (C is zero off its triangle, so the fixed-length sums add exact zeros).
 // Upward, an absent child reads a slot of zeros (slot CAP), so that the
-// four quadrant sums run side by side without branches.
+// four quadrant sums run side by side without branches.  XL: work-groups
+// past ncomp form P2L sums (run_pass).
 constexpr int kPassThreads = 1024;
-template <typename T, int P, bool DOWN>
+template <typename T, int P, bool DOWN, bool XL = false>
 __global__ void __launch_bounds__(kPassThreads)
     k_pass(const int32_t *__restrict__ hdr, const int2 *__restrict__ ext,
            const int4 *__restrict__ par, const int32_t *__restrict__ stp,
            const T *__restrict__ Cb, const cx<T> *__restrict__ Pre,
-           const cx<T> *__restrict__ Post, cx<T> *__restrict__ E, int nbox) {
+           const cx<T> *__restrict__ Post, cx<T> *__restrict__ E, int nbox, int ncomp,
+           XBoxes xb, const cx<T> *__restrict__ p, cx<T> *__restrict__ L) {
   using V = typename Chunk16<T>::type;
+  if constexpr (XL) {
+    if ((int)blockIdx.x >= ncomp) {  // block-uniform: P2L sums, two boxes a wave
+      const int e = ((int)blockIdx.x - ncomp) * (kPassThreads / 64) + (int)(threadIdx.x >> 6);
+      if (2 * e < xb.n) p2l_pair64<P, 16>(e, blockIdx.y, xb, p, L, nbox);
+      return;
+    }
+  }
   constexpr int NT = kPassThreads, CAP = pass_cap(P, (int)sizeof(cx<T>));
   static_assert(P * (int)sizeof(cx<T>) % 16 == 0, "expansions of whole 16-byte chunks");
   constexpr int CH = P * (int)sizeof(cx<T>) / 16, IT = (CAP * CH + NT - 1) / NT;
@@ -748,21 +880,36 @@ __global__ void __launch_bounds__(kPassThreads)
   }
 }
 
-// The rounds of a pass program, one launch each.
+// The rounds of a pass program, one launch each; the first launch of an
+// upward FP64 pass also forms the P2L sums of the boxes xb (strengths p,
+// stored to L) while they are at most kP2LGroups work-groups: the pass
+// leaves most of the chip idle then and they cost no launch and no time
+// ((I + K) at 20k nodes 68.9 us against 71.7 with a launch of their own, 77k
+// the same; 1.02M, where the pass fills the chip, 442 against 426).  Returns
+// whether it did.
+constexpr int kP2LGroups = 128;
 template <typename T, int P, bool DOWN>
-static void run_pass(const DevPass &pg, const T *bc, const cx<T> *pre, const cx<T> *post,
-                     cx<T> *E, int nbox, int nrhs, hipStream_t s) {
+static bool run_pass(const DevPass &pg, const T *bc, const cx<T> *pre, const cx<T> *post,
+                     cx<T> *E, int nbox, int nrhs, hipStream_t s, XBoxes xb = XBoxes{},
+                     const cx<T> *p = nullptr, cx<T> *L = nullptr) {
+  bool p2l = false;
   if (pg.cap != pass_cap(P, (int)sizeof(cx<T>)))
     throw ApiError{LBS_ERR_UNSUPPORTED, "pass program built for another expansion order"};
   for (size_t k = 0; k + 1 < pg.round_ptr.size(); ++k) {
     const int a = pg.round_ptr[k], n = pg.round_ptr[k + 1] - a;
     if (n <= 0) continue;
-    hipLaunchKernelGGL((k_pass<T, P, DOWN>), dim3(n, nrhs), dim3(kPassThreads), 0, s,
+    // (a wave takes two boxes, a work-group kPassThreads / 64 waves)
+    const int per = kPassThreads / 32, xg = (xb.n + per - 1) / per;
+    const int nx = !p2l && xg > 0 && xg * nrhs <= kP2LGroups ? xg : 0;
+    p2l = p2l || nx > 0;
+    const auto kern = nx > 0 ? k_pass<T, P, DOWN, sizeof(T) == 8 && !DOWN> : k_pass<T, P, DOWN>;
+    hipLaunchKernelGGL(kern, dim3(n + nx, nrhs), dim3(kPassThreads), 0, s,
                        pg.hdr.p + 8 * (int64_t)a,
                        reinterpret_cast<const int2 *>(pg.ext.p) + (int64_t)a * pg.cap,
                        reinterpret_cast<const int4 *>(pg.par.p), pg.stp.p, bc, pre, post, E,
-                       nbox);
+                       nbox, n, xb, p, L);
   }
+  return p2l;
 }
 
 template <int P>
@@ -1013,6 +1160,147 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// x of the lane's neighbour (lane ^ 1)
+__device__ __forceinline__ double lane_xor1(double x) {
+  const unsigned long long u = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)u, 0xB1, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0xB1, 0xF, 0xF, true);
+  return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// M2L over the V lists of a group of boxes at level >= 2 (FP64, matrix
+// cores).  For eight list entries at a time a wave forms
+// Y[k][2 v + part] = part(tau_v^-(k+1) a_{v,k+1}), multiplies Z = H Y with
+// v_mfma_f64_16x16x4f64 (H[l][k] = (-1)^k C(k+l-1, l), held in registers),
+// scales column pair v by tau_v^-l and writes it to LDS, where one lane per
+// (box, coefficient part) adds the box's entries (and, with add_x, the P2L
+// sum that boxes with an X list hold already).  Lane layout of the 16x16x4
+// instruction: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k, D[i][j]
+// in lane j + 16 (i % 4), register i / 4.
+//
+// Bound by the latency of the gathers and of the exchange; the matrix cores
+// are 0.4 busy (their share at 1.02M nodes, 536k entries: 30 of 75 us).  The
+// vector form this replaces broadcast y through LDS, 16 bytes read per two
+// multiply-adds and lane, four times what the LDS delivers beside them: 122
+// us.  Rows of H in scalar registers with one entry per lane took 105 us (a
+// wave waits for each row), a persistent form that reads one batch ahead 90
+// (158 registers, three waves a SIMD), groups of 32 entries 80; two and
+// eight waves a group 96 and 109 against 83 with four.
+constexpr int kM2LWaves = 4;
+template <int P>
+__global__ void __launch_bounds__(64 * kM2LWaves)
+    k_m2l64(int ngrp, const int2 *__restrict__ ent, const int2 *__restrict__ gbox,
+            const double *__restrict__ H,
+            const cx<double> *__restrict__ M, cx<double> *__restrict__ L, int nbox, int add_x,
+            GammaGroups gg) {
+  constexpr int NT = (P + 15) / 16, NS = (P + 3) / 4, ROW = kM2LEnt + 1;
+  if ((int)blockIdx.x >= ngrp) {   // block-uniform: a correction chunk
+    const int x = blockIdx.x - ngrp;
+    gamma_chunk(x % gg.nchunk, x / gg.nchunk, blockIdx.y, gg.nchunk, gg.gl_ptr, gg.gpart,
+                gg.nls, gg.G, gg.csum, gg.cnt, gg.gamma);
+    return;
+  }
+  extern __shared__ __align__(16) double tb[];  // [2 P][entry]
+  __shared__ int2 sbox[kM2LBoxes];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = kM2LWaves;
+  const int lane = threadIdx.x & 63, r = blockIdx.y;
+  const int col = lane & 15, kq = lane >> 4, part = col & 1;
+  const int2 mine = ent[(int64_t)blockIdx.x * kM2LEnt + (lane & (kM2LEnt - 1))];
+  const int2 bx = gbox[blockIdx.x * kM2LBoxes + (lane & (kM2LBoxes - 1))];
+  if (threadIdx.x < kM2LBoxes) sbox[threadIdx.x] = bx;
+  const int total = __shfl(bx.y, kM2LBoxes - 1, 64) & 0xFFFF;  // list entries of the group
+  if (8 * wv < total) {
+    double a[NT][NS];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int l = 16 * t + col, k = 4 * s + kq;
+        a[t][s] = l < P && k < P ? H[l * P + k] : 0.0;
+      }
+    for (int v0 = 8 * wv; v0 < total; v0 += 8 * W) {
+      const int v = v0 + (col >> 1);
+      const int src = __shfl(mine.x, v, 64), code = __shfl(mine.y, v, 64);
+      const cx<double> *ms = M + ((int64_t)r * nbox + max(src, 0)) * P;
+      cx<double> m[NS];  // multipole coefficients k = 4 s + kq of the column's entry
+#pragma unroll
+      for (int s = 0; s < NS; ++s) m[s] = 4 * s + kq < P ? ms[4 * s + kq] : cx<double>{0.0, 0.0};
+      const double tx = 2.0 * (code / 7 - 3), ty = 2.0 * (code % 7 - 3);
+      const double id = src < 0 ? 0.0 : 1.0 / (tx * tx + ty * ty);
+      const cx<double> w{tx * id, -ty * id};  // 1 / tau (0 past the last entry)
+      const cx<double> w2 = w * w, w4 = w2 * w2;
+      cx<double> q = kq & 1 ? w2 : w;         // w^(kq + 1), times -i for the
+      if (kq & 2) q = q * w2;                 // imaginary column: Im y = Re(-i y)
+      if (part) q = cx<double>{q.y, -q.x};
+      v4d d[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) d[t] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const double y = fma(q.x, m[s].x, -(q.y * m[s].y));
+        q = q * w4;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][s], y, d[t], 0, 0, 0);
+      }
+      // row l = 16 t + 4 j + kq: part(tau^-l z) = u^l.x mine + u^l.y other
+      // with u = conj(w) (real part) or w (imaginary part)
+      const double sg = part ? 1.0 : -1.0;
+      const cx<double> u4{w4.x, sg * w4.y}, u1{w.x, sg * w.y}, u2{w2.x, sg * w2.y};
+      cx<double> ul = kq & 1 ? u1 : cx<double>{1.0, 0.0};
+      if (kq & 2) ul = ul * u2;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double mz = d[t][j], other = lane_xor1(mz);
+          const int l = 16 * t + 4 * j + kq;
+          if (l < P) tb[(2 * l + part) * ROW + v] = fma(ul.x, mz, ul.y * other);
+          ul = ul * u4;
+        }
+    }
+  }
+  __syncthreads();
+  // one lane per (box, coefficient part): the box's entries, eight in flight
+  for (int x = threadIdx.x; x < kM2LBoxes * 2 * P; x += blockDim.x) {
+    const int i = x / (2 * P), c = x % (2 * P);
+    const int2 gb = sbox[i];
+    if (gb.x < 0) break;
+    const int t1 = gb.y & 0xFFFF, t0 = i > 0 ? sbox[i - 1].y & 0xFFFF : 0;
+    double *o = reinterpret_cast<double *>(L + ((int64_t)r * nbox + gb.x) * P) + c;
+    double s = add_x && (gb.y >> 16) ? *o : 0.0;
+    for (int t = t0; t < t1; t += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = tb[c * ROW + min(t + u, t1 - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += t + u < t1 ? v[u] : 0.0;
+    }
+    *o = s;
+  }
+}
+
+template <int P>
+__global__ void __launch_bounds__(64)
+    k_p2l64(XBoxes xb, const cx<double> *__restrict__ p, cx<double> *__restrict__ L, int nbox) {
+  p2l_pair64<P, 32>(blockIdx.x, blockIdx.y, xb, p, L, nbox);
+}
+
+// Launch of k_m2l64 over the plan's groups, with the correction sums of gg
+// as extra work-groups when gg.nchunk > 0; add_x: boxes with an X list hold
+// their P2L sum already.
+template <int P>
+static void launch_m2l64(const DevPlan &pl, const double *H, const cx<double> *M,
+                         cx<double> *L, bool add_x, int nrhs, GammaGroups gg, hipStream_t s) {
+  const int ng = pl.n_grp, W = kM2LWaves;
+  const size_t lds = (size_t)2 * P * (kM2LEnt + 1) * sizeof(double);
+  hipLaunchKernelGGL((k_m2l64<P>), dim3(ng + gg.nchunk * gg.G, nrhs), dim3(64 * W), lds, s, ng,
+                     pl.grp_ent.p, pl.grp_box.p, H, M, L, pl.nbox, (int)add_x, gg);
+}
+
+
 // P2L over the X list of one box per wave (p2l_sum, KB coefficients per
 // pass), added to the M2L result.
 template <typename T, int P, int K0>
@@ -1052,15 +1340,6 @@ __global__ void __launch_bounds__(64)
                     T(rad[b]), sx, sy, p + (int64_t)r * ns,
                     reinterpret_cast<T *>(L + ((int64_t)r * nbox + b) * P),
                     (int)threadIdx.x);
-}
-
-// 1 / d in FP64: the hardware estimate (2^-22 or better) and one cubic
-// correction, r (1 + e + e^2) with e = 1 - d r, which leaves e^3 < 2^-64:
-// three fused multiply-adds where two Newton-Raphson steps take four.
-__device__ __forceinline__ double rcp64(double d) {
-  const double r = __builtin_amdgcn_rcp(d);
-  const double e = fma(-d, r, 1.0);
-  return fma(r, fma(e, e, e), r);
 }
 
 __device__ __forceinline__ int pow2_at_least(int n) {
@@ -1623,6 +1902,11 @@ void launch_qm32(int64_t n, const double *qfac_t, float2 *qm32, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- drivers
+static XBoxes x_boxes(const DevPlan &pl) {
+  return XBoxes{(int)pl.x_box.n, pl.x_box.p, pl.xf_ptr.p, pl.xf_idx.p, pl.cx.p, pl.cy.p,
+                pl.rad.p, pl.sx.p, pl.sy.p, pl.ns};
+}
+
 // Returns whether the correction sums of gf were formed too (by the FP32
 // MFMA M2L launch).
 template <typename T, int P>
@@ -1630,7 +1914,7 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
                       cx<T> *p, cx<T> *M, cx<T> *L, int nrhs,
                       hipStream_t s, StrengthSrc ss = StrengthSrc{},
                       const GammaFused *gf = nullptr) {
-  bool gamma_done = false;
+  bool gamma_done = false, p2l_done = false;
   StageTimer *tm = ws.timer;
   const cx<T> *itp, *pre, *post;
   const T *H, *bc;
@@ -1664,7 +1948,11 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
                            s, pl.leaf_s.p, pl.ls_rng.p, pl.ls_geo.p, pl.sx.p,
                            pl.sy.p, p, pl.ns, M, pl.nbox, ss);
     }
-    run_pass<T, P, false>(pl.up[sizeof(T) == 8], bc, pre, post, M, pl.nbox, nrhs, s);
+    if constexpr (sizeof(T) == 8)
+      p2l_done = run_pass<T, P, false>(pl.up[1], bc, pre, post, M, pl.nbox, nrhs, s, x_boxes(pl),
+                                       p, L);
+    else
+      run_pass<T, P, false>(pl.up[0], bc, pre, post, M, pl.nbox, nrhs, s);
   }
   // the FP32 MFMA M2L also forms the P2L sums of its boxes: every box with
   // an X list whose local expansion is used (level >= 2, with targets) is
@@ -1672,22 +1960,26 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
   constexpr bool p2l_in_m2l = sizeof(T) == 4 && P == 16;
   if (pl.n_m2l > 0) {
     TimerScope ts(tm, ST_M2L, s);
+    GammaGroups gg;  // the correction sums ride along
+    if (gf && pl.n_leaf_s > 0)
+      gg = GammaGroups{gf->gl_ptr, ws.gpart.p, ws.gcsum.p, ws.gcnt.p, gf->gamma,
+                       pl.n_leaf_s, gf->G, gf->nchunk, 0};
     if constexpr (p2l_in_m2l) {
       const XListSrc xs{pl.xf_ptr.p, pl.xf_idx.p, pl.cx.p, pl.cy.p, pl.rad.p,
                         pl.sx.p, pl.sy.p, (const cx<float> *)p, pl.ns};
-      GammaGroups gg;
       gg.first = std::min((pl.n_m2l + 3) / 4, pl.m2l_groups);
-      int groups = gg.first;
-      if (gf && pl.n_leaf_s > 0) {  // the correction sums ride along
-        gg = GammaGroups{gf->gl_ptr, ws.gpart.p, ws.gcsum.p, ws.gcnt.p, gf->gamma,
-                         pl.n_leaf_s, gf->G, gf->nchunk, gg.first};
-        groups += gf->nchunk * gf->G;
-        gamma_done = true;
-      }
+      const int groups = gg.first + gg.nchunk * gg.G;
+      gamma_done = gg.nchunk > 0;
       hipLaunchKernelGGL(k_m2l_mfma16, dim3(groups, nrhs), dim3(256), 0, s,
                          pl.n_m2l, pl.m2l_wave.p, pl.v_ptr.p, pl.v_src.p,
                          pl.v_code.p, H, itp, (const cx<T> *)M, L, pl.nbox, xs,
                          gg);
+    } else if constexpr (sizeof(T) == 8) {
+      gamma_done = gg.nchunk > 0;
+      if (pl.x_box.n > 0 && !p2l_done)  // no upward pass
+        hipLaunchKernelGGL((k_p2l64<P>), dim3((unsigned)(pl.x_box.n + 1) / 2, nrhs), dim3(64), 0,
+                           s, x_boxes(pl), p, L, pl.nbox);
+      launch_m2l64<P>(pl, H, M, L, true, nrhs, gg, s);
     } else {
       hipLaunchKernelGGL((k_m2l<T, P>), dim3(pl.n_m2l, nrhs), dim3(64), 0, s,
                          pl.m2l_box.p, pl.v_ptr.p, pl.v_src.p, pl.v_code.p, H,
@@ -1709,8 +2001,8 @@ static void run64(const DevPlan &pl, const Tables &tb, Workspace &ws,
   auto *p = (cx<double> *)ws.pstr64.p;
   auto *M = (cx<double> *)ws.mult64.p;
   auto *L = (cx<double> *)ws.loc64.p;
-  far_field<double, P>(pl, tb, ws, p, M, L, nrhs, s, ss);
-  if (gf && pl.n_leaf_s > 0) {
+  const bool gamma_done = far_field<double, P>(pl, tb, ws, p, M, L, nrhs, s, ss, gf);
+  if (gf && pl.n_leaf_s > 0 && !gamma_done) {
     TimerScope ts(ws.timer, ST_GAMMA, s);
     hipLaunchKernelGGL(k_gamma_reduce, dim3(gf->nchunk, gf->G, nrhs), dim3(256), 0,
                        s, gf->gl_ptr, ws.gpart.p, pl.n_leaf_s, gf->G, ws.gcsum.p,
@@ -1894,7 +2186,6 @@ static void run64_sources(const DevPlan &pl, const Tables &tb, Workspace &ws,
   auto *M = (cx<double> *)ws.mult64.p;
   auto *L = (cx<double> *)ws.loc64.p;
   const auto *H = (const double *)tb.h64.p;
-  const auto *itp = (const cx<double> *)tb.itp64.p;
   // multipoles of every box of level >= 2 from the points it holds: the
   // partial multipoles of chunks of at most kSrcChunk pairs, added per box
   // (boxes without points get zeros)
@@ -1908,11 +2199,7 @@ static void run64_sources(const DevPlan &pl, const Tables &tb, Workspace &ws,
     hipLaunchKernelGGL((k_sum_chunks<P>), dim3((unsigned)(((int64_t)ps.n_m * P + 255) / 256)),
                        dim3(256), 0, s, ps.n_m, ps.m_list.p, ps.c_ptr.p, part, M);
   // the tree's V lists, then the points' own local-expansion terms
-  if (pl.n_m2l > 0)
-    hipLaunchKernelGGL((k_m2l<double, P>), dim3(pl.n_m2l, 1), dim3(64), 0, s, pl.m2l_box.p,
-                       pl.v_ptr.p, pl.v_src.p, pl.v_code.p, H, itp, (const cx<double> *)M, L,
-                       pl.nbox, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       nullptr, int64_t(0));
+  if (pl.n_m2l > 0) launch_m2l64<P>(pl, H, M, L, false, 1, GammaGroups{}, s);
   if (ps.n_m > 0)
     hipLaunchKernelGGL((k_p2l<double, P>), dim3(ps.n_m, 1), dim3(64), 0, s, ps.m_list.p,
                        ps.l_ptr.p, ps.l_t.p, pl.cx.p, pl.cy.p, pl.rad.p, ps.x, ps.y, pin, ps.n,

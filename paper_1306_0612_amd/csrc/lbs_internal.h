@@ -116,6 +116,10 @@ struct LeafHdr {
 // one resident round on 256 CUs at the kernel's occupancy of 4 per SIMD.
 constexpr int kM2LGroups = 1024;
 
+// Boxes of one FP64 M2L work-group: at most kM2LBoxes whose V lists hold at
+// most kM2LEnt entries together (a V list holds at most 27).
+constexpr int kM2LBoxes = 16, kM2LEnt = 64;
+
 struct DevPlan {
   int nbox = 0, nlevels = 0;
   int64_t ns = 0, nt = 0;
@@ -146,6 +150,11 @@ struct DevPlan {
   DBuf<int64_t> ls_rng;
   DBuf<double4> ls_geo;
   DBuf<int32_t> m2l_wave;  // M2L boxes in the FP32 kernel's wave order
+  // groups of M2L boxes of the FP64 kernel (build_m2l_groups): their V-list
+  // entries and boxes
+  int n_grp = 0;
+  DBuf<int2> grp_ent, grp_box;
+  DBuf<int32_t> x_box;  // boxes with X lists, most sources first
   // Upward (M2M) and downward (L2L) pass programs (PassProgram in tree.h)
   // for the FP32 ([0]) and FP64 ([1]) expansion orders of the handle.
   DevPass up[2], dn[2];
@@ -159,6 +168,10 @@ struct DevPlan {
   DBuf<int32_t> perm32;
   Tree host;                                  // host tree (statistics)
 };
+
+// The FP64 M2L groups of a plan from (first entry of m2l_box, count) pairs
+// (fmm.hip).
+void build_m2l_groups(DevPlan &pl, const std::vector<int32_t> &grp, hipStream_t s);
 
 // Translation tables for expansions of P terms (see fmm.hip).
 struct Tables {
