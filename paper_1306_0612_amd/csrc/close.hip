@@ -21,6 +21,7 @@
 // differentiation matrix (1/2) (-1)^(i-j) cot((t_i - t_j)/2) for even N,
 // csc for odd N).  The evaluation pass has already summed the trapezoidal
 // v at every target, so each pair adds -s_k Re(v_close - v_trap).  FP64.
+#include <algorithm>
 #include <cmath>
 
 #include "cplx.h"
@@ -37,71 +38,98 @@ __device__ __forceinline__ double wsum(double v) {
   return v;
 }
 
-// V for the nodes of island act[blockIdx.x], column blockIdx.y; node data
-// staged through LDS in tiles of 256.
+// V for nodes kBvNodes blockIdx.z .. of island act[blockIdx.x], column
+// blockIdx.y.  Lane l of every wave holds nodes l and l + 64 of the tile;
+// the island's nodes j pass through LDS in tiles of 256, of which each wave
+// takes a quarter, and the waves' sums meet in LDS.  The differentiation
+// weights depend on i - j alone: 383 of them per pair of tiles, formed once
+// in LDS instead of a sincospi and a division per node pair (which took most
+// of 1.95 ms for 2000 islands of 512 nodes, now 0.37; one work-group per
+// island also left few islands on few compute units: 0.46 ms at 300 x 256,
+// now 0.05).  Bound by the FP64 vector units.
+constexpr int kBvNodes = 128, kBvTile = 256;
 __global__ void __launch_bounds__(256)
     k_close_bvals(const int32_t *__restrict__ act,
                   const int64_t *__restrict__ offs,
                   const double *__restrict__ xi, const double *__restrict__ dxi,
                   const double *__restrict__ sigma, int64_t ldx,
                   double *__restrict__ V, int64_t ldv) {
-  __shared__ double ts[256], tx[256], ty[256], tdx[256], tdy[256];
-  const int k = act[blockIdx.x];
-  const int r = blockIdx.y;
+  __shared__ double2 tz[kBvTile], td[kBvTile];  // xi_j, xi'_j
+  __shared__ double ts[kBvTile];                // sigma_j
+  __shared__ double wt[kBvNodes + kBvTile];     // weight of i - j
+  const int k = act[blockIdx.x], r = blockIdx.y, i0 = kBvNodes * (int)blockIdx.z;
   const int64_t a = offs[k];
   const int n = (int)(offs[k + 1] - a);
+  if (i0 >= n) return;  // block-uniform
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double h = kTwoPi / (double)n;
   const double *sg = sigma + (int64_t)r * ldx + a;
   const bool even = (n & 1) == 0;
-  for (int i0 = 0; i0 < n; i0 += 256) {
-    const int i = i0 + threadIdx.x;
-    const bool live = i < n;
-    double si = 0.0, xr = 0.0, xim = 0.0;
-    if (live) {
-      si = sg[i];
-      xr = xi[2 * (a + i)];
-      xim = xi[2 * (a + i) + 1];
-    }
-    double ds = 0.0;           // spectral derivative of sigma at node i
-    double vr = 0.0, vi = 0.0; // sum of (sigma_j - sigma_i) xi'_j / (xi_j - xi_i)
-    for (int j0 = 0; j0 < n; j0 += 256) {
-      __syncthreads();
-      const int jl = j0 + threadIdx.x;
-      if (jl < n) {
-        ts[threadIdx.x] = sg[jl];
-        tx[threadIdx.x] = xi[2 * (a + jl)];
-        ty[threadIdx.x] = xi[2 * (a + jl) + 1];
-        tdx[threadIdx.x] = dxi[2 * (a + jl)];
-        tdy[threadIdx.x] = dxi[2 * (a + jl) + 1];
-      }
-      __syncthreads();
-      if (!live) continue;
-      const int jn = min(256, n - j0);
-      for (int jj = 0; jj < jn; ++jj) {
-        const int j = j0 + jj;
-        if (j == i) continue;
-        const int m = i - j;
+  double si[2], xr[2], xm[2], ds[2], vr[2], vi[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int i = min(i0 + lane + 64 * q, n - 1);
+    si[q] = sg[i];
+    xr[q] = xi[2 * (a + i)];
+    xm[q] = xi[2 * (a + i) + 1];
+    ds[q] = 0.0;           // spectral derivative of sigma at node i
+    vr[q] = vi[q] = 0.0;   // sum of (sigma_j - sigma_i) xi'_j / (xi_j - xi_i)
+  }
+  for (int j0 = 0; j0 < n; j0 += kBvTile) {
+    __syncthreads();
+    const int jl = j0 + tid;
+    const bool in = jl < n;  // past the end: sigma and xi' zero, weight below
+    ts[tid] = in ? sg[jl] : 0.0;
+    tz[tid] = in ? make_double2(xi[2 * (a + jl)], xi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
+    td[tid] = in ? make_double2(dxi[2 * (a + jl)], dxi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
+    for (int x = tid; x < kBvNodes + kBvTile; x += 256) {
+      const int m = i0 - j0 + x - (kBvTile - 1);  // i - j
+      double w = 0.0;
+      if (m != 0 && m > -n && m < n) {
         double sn, cs;
         sincospi((double)m / (double)n, &sn, &cs);
-        const double sgn = (m & 1) ? -0.5 : 0.5;
-        ds += sgn * (even ? cs / sn : 1.0 / sn) * ts[jj];
-        const double dx = tx[jj] - xr, dy = ty[jj] - xim;
-        const double inv = 1.0 / (dx * dx + dy * dy);
-        const double ds_j = ts[jj] - si;
-        // (dxi_j / (xi_j - xi_i)) = dxi_j * conj(d) / |d|^2
-        const double qr = (tdx[jj] * dx + tdy[jj] * dy) * inv;
-        const double qi = (tdy[jj] * dx - tdx[jj] * dy) * inv;
-        vr += ds_j * qr;
-        vi += ds_j * qi;
+        w = ((m & 1) ? -0.5 : 0.5) * (even ? cs / sn : 1.0 / sn);
+      }
+      wt[x] = w;
+    }
+    __syncthreads();
+    const int ja = wv * (kBvTile / 4), jb = min(ja + kBvTile / 4, n - j0);
+#pragma unroll 2
+    for (int jj = ja; jj < jb; ++jj) {
+      const double2 z = tz[jj], d = td[jj];
+      const double sj = ts[jj];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        ds[q] += wt[lane + 64 * q + kBvTile - 1 - jj] * sj;
+        const double dx = z.x - xr[q], dy = z.y - xm[q];
+        // (a node's own term: sigma_j - sigma_i = 0 times a finite value)
+        const double d2 = fma(dx, dx, fma(dy, dy, 1e-300));
+        const double rc = __builtin_amdgcn_rcp(d2), e = fma(-d2, rc, 1.0);
+        const double g = (sj - si[q]) * fma(rc, fma(e, e, e), rc);
+        // dxi_j / (xi_j - xi_i) = dxi_j * conj(d) / |d|^2
+        vr[q] += g * fma(d.x, dx, d.y * dy);
+        vi[q] += g * fma(d.y, dx, -(d.x * dy));
       }
     }
-    if (live) {
+  }
+  // the four waves' sums: [value][wave][lane], in the tile buffers
+  __syncthreads();
+  double *red = reinterpret_cast<double *>(tz);  // 4 kBvTile doubles: 4 waves x 64 x (ds + vr, vi)
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    red[wv * 64 + lane] = vr[q] + ds[q];
+    red[256 + wv * 64 + lane] = vi[q];
+    __syncthreads();
+    const int i = i0 + lane + 64 * q;
+    if (wv == 0 && i < n) {
+      const double sr = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
+      const double sm = (red[256 + lane] + red[320 + lane]) + (red[384 + lane] + red[448 + lane]);
       // V = h (sum + ds) / (2 pi i) = -i h (sum + ds) / (2 pi)
-      const double sr = vr + ds, sim = vi;
       const double f = h / kTwoPi;
-      V[2 * ((int64_t)r * ldv + a + i)] = f * sim;
+      V[2 * ((int64_t)r * ldv + a + i)] = f * sm;
       V[2 * ((int64_t)r * ldv + a + i) + 1] = -f * sr;
     }
+    __syncthreads();
   }
 }
 
@@ -170,7 +198,10 @@ void launch_close_eval(const Geometry &g, const ClosePlan &cp, int nrhs,
                        const double *sigma, int64_t ldx, double *V,
                        double *u, int64_t ldu, hipStream_t s) {
   if (cp.n_tgt == 0) return;
-  hipLaunchKernelGGL(k_close_bvals, dim3(cp.n_act, nrhs), dim3(256), 0, s,
+  int maxn = 0;
+  for (int32_t v : g.nodes) maxn = std::max(maxn, (int)v);
+  hipLaunchKernelGGL(k_close_bvals, dim3(cp.n_act, nrhs, (maxn + kBvNodes - 1) / kBvNodes),
+                     dim3(256), 0, s,
                      cp.act.p, g.doffs.p, g.xi.p, g.dxi.p, sigma, ldx, V, g.N);
   hipLaunchKernelGGL(k_close_correct, dim3((cp.n_tgt + 3) / 4, nrhs),
                      dim3(256), 0, s, cp.n_tgt, cp.z.p, cp.out.p, cp.ptr.p,
