@@ -49,8 +49,9 @@ __device__ int descend(double x, double y, int r, int max_level, const double *_
     const bool gx = x >= bx, gy = y >= by;
     const int c0 = child0[b], nc = nchild[b];
     int f = -1;
-    for (int k = 0; k < nc; ++k) {
-      const int ch = c0 + k;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // clamped: the four children's loads go out together
+      const int ch = c0 + min(k, nc - 1);
       if ((cxv[ch] > bx) == gx && (cyv[ch] > by) == gy) f = ch;
     }
     if (f < 0) break;  // that quadrant holds no nodes
@@ -114,6 +115,7 @@ __device__ __forceinline__ double direct_sum(double x, double y, int64_t a0, int
                                              const double *__restrict__ sy,
                                              const cx<double> *__restrict__ p) {
   double f = 0.0;
+#pragma unroll 4
   for (int64_t j = a0; j < a1; ++j) {
     const double dx = x - sx[j], dy = y - sy[j];
     const double d2 = fma(dx, dx, fma(dy, dy, 1e-300));
@@ -123,17 +125,23 @@ __device__ __forceinline__ double direct_sum(double x, double y, int64_t a0, int
   return f;
 }
 
+// sum_k a_k w^k by Horner's scheme
+template <int P>
+__device__ __forceinline__ cx<double> series_at(const cx<double> *__restrict__ a, cx<double> w) {
+  cx<double> acc = a[P - 1];
+#pragma unroll
+  for (int k = P - 2; k >= 0; --k) acc = cfma(acc, w, a[k]);
+  return acc;
+}
+
 // Re of box b's multipole at z: sum_k a_k rho^(k+1), rho = rad_b / (z - c_b)
 template <int P>
 __device__ __forceinline__ double multipole_at(double x, double y, int b, const TreeView &t,
                                                const cx<double> *__restrict__ M) {
   const double dx = x - t.cx[b], dy = y - t.cy[b];
   const double ir = t.rad[b] * recip_nr(fma(dx, dx, dy * dy));
-  const cx<double> rho{dx * ir, -dy * ir};
-  const cx<double> *a = M + (int64_t)b * P;
-  cx<double> acc = a[P - 1];
-  for (int k = P - 2; k >= 0; --k) acc = cfma(acc, rho, a[k]);
-  return (acc * rho).x;
+  const cx<double> w{dx * ir, -dy * ir};
+  return (series_at<P>(M + (int64_t)b * P, w) * w).x;
 }
 
 // c's subtree as seen from z, walked depth first without a stack (children
@@ -167,33 +175,44 @@ __device__ void walk_subtree(double x, double y, int c, const TreeView &t, Vis &
 
 // The sources the local expansion of B leaves out, for z in B (B < 0: z
 // outside the root square, or B the root: every source): the subtrees of
-// B's colleagues and the coarser leaves adjacent to B.
+// B's colleagues and the coarser leaves adjacent to B.  near_square(o) finds
+// them for square o = 0 .. 8 of B's 3 x 3 neighbourhood (4 is B itself):
+// the box, or -1, and whether it is a coarser leaf (which may cover several
+// squares and counts once).  The descent starts at the lowest ancestor of B
+// that holds the square, two levels up on average.
+__device__ int near_square(int o, int B, int root, const TreeView &t, bool &coarse) {
+  coarse = false;
+  if (B < 0 || t.lev[B] == 0) return o == 4 ? root : -1;
+  if (o == 4) return B;
+  const int l = t.lev[B];
+  const double h = t.rad[B];
+  const double qx = t.cx[B] + 2.0 * h * (double)(o % 3 - 1);
+  const double qy = t.cy[B] + 2.0 * h * (double)(o / 3 - 1);
+  int a = B;
+  do a = t.parent[a];
+  while (a != root && (fabs(qx - t.cx[a]) > t.rad[a] || fabs(qy - t.cy[a]) > t.rad[a]));
+  const int c = descend(qx, qy, a, l, t.cx, t.cy, t.rad, t.lev, t.child0, t.nchild, t.leaf);
+  if (c < 0 || t.lev[c] == l) return c;
+  coarse = true;
+  return t.leaf[c] ? c : -1;  // -1: no nodes in that square
+}
+
 template <class Vis>
 __device__ void walk_near(double x, double y, int B, int root, const TreeView &t, Vis &v) {
-  if (B < 0 || t.lev[B] == 0) {
-    walk_subtree(x, y, root, t, v);
-    return;
-  }
-  const int l = t.lev[B];
-  const double h = t.rad[B], bx = t.cx[B], by = t.cy[B];
-  walk_subtree(x, y, B, t, v);
-  int coarse[8];  // at most one per neighbour square
-  int nco = 0;
-  for (int o = 0; o < 9; ++o) {
-    if (o == 4) continue;  // B itself
-    const double qx = bx + 2.0 * h * (double)(o % 3 - 1);
-    const double qy = by + 2.0 * h * (double)(o / 3 - 1);
-    const int c = descend(qx, qy, root, l, t.cx, t.cy, t.rad, t.lev, t.child0, t.nchild, t.leaf);
+  int seen[8];  // coarser leaves, at most one per neighbour square
+  int ns = 0;
+  for (int k = 0; k < 9; ++k) {
+    bool coarse;
+    const int c = near_square(k == 0 ? 4 : k <= 4 ? k - 1 : k, B, root, t, coarse);
     if (c < 0) continue;
-    if (t.lev[c] == l) {  // a colleague
+    if (!coarse) {
       walk_subtree(x, y, c, t, v);
       continue;
     }
-    if (!t.leaf[c]) continue;  // no nodes in that square
-    bool seen = false;         // a coarser leaf adjacent to B
-    for (int k = 0; k < nco; ++k) seen = seen || coarse[k] == c;
-    if (seen) continue;
-    coarse[nco++] = c;
+    bool dup = false;
+    for (int e = 0; e < ns; ++e) dup = dup || seen[e] == c;
+    if (dup) continue;
+    seen[ns++] = c;
     v.direct(c);
   }
 }
@@ -207,31 +226,57 @@ struct SumVisitor {
   __device__ void direct(int b) { f += direct_sum(x, y, t.s0[b], t.s1[b], t.sx, t.sy, p); }
 };
 
-// One thread per target (targets sorted by their box), right-hand side
-// blockIdx.y: out[r ldy + idx] = scale Re Psi(z).
+// Nine waves per 64 targets (sorted by their box), right-hand side
+// blockIdx.y: wave o takes square o of the 3 x 3 neighbourhood of its
+// targets' boxes (wave 4 the local expansions as well), and
+// out[r ldy + idx] = scale Re Psi(z) sums the nine.  Bound by the latency of
+// the walks (dependent loads of box data): one thread per target walked the
+// nine squares in turn, each found from the root, on 1.5 waves per SIMD at
+// 1e5 targets (0.84 ms over 1M nodes; the nine waves 0.45 ms).  Nine lanes
+// of one wave per target take as long there, but twice as long at 4e5
+// targets of a small problem: neighbouring targets of one box walk the same
+// boxes, and a wave of one square keeps their lanes together.
+constexpr int kEvSquares = 9;
 template <int P>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64 * kEvSquares)
     k_eval_points(int64_t n, const double *__restrict__ tx, const double *__restrict__ ty,
                   const int32_t *__restrict__ tbox, const int32_t *__restrict__ troot,
                   const int64_t *__restrict__ tidx, TreeView t, const cx<double> *__restrict__ p,
                   int64_t ns, const cx<double> *__restrict__ M, const cx<double> *__restrict__ L,
                   int nbox, double *__restrict__ out, int64_t ldy, double scale) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int r = blockIdx.y;
-  const double x = tx[i], y = ty[i];
-  const int B = tbox[i], root = troot[i];
-  SumVisitor<P> v{x, y, 0.0, t, p + (int64_t)r * ns, M + (int64_t)r * nbox * P};
-  if (B >= 0 && t.lev[B] >= 2) {
-    const double ir = 1.0 / t.rad[B];
-    const cx<double> w{(x - t.cx[B]) * ir, (y - t.cy[B]) * ir};
-    const cx<double> *Lb = L + ((int64_t)r * nbox + B) * P;
-    cx<double> acc = Lb[P - 1];
-    for (int k = P - 2; k >= 0; --k) acc = cfma(acc, w, Lb[k]);
-    v.f = acc.x;
+  __shared__ int leaf[kEvSquares][64];
+  __shared__ double part[kEvSquares][64];
+  const int lane = threadIdx.x & 63, sq = threadIdx.x >> 6, r = blockIdx.y;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool on = i < n;
+  SumVisitor<P> v{0.0, 0.0, 0.0, t, p + (int64_t)r * ns, M + (int64_t)r * nbox * P};
+  int B = -1, c = -1;
+  bool coarse = false;
+  if (on) {
+    v.x = tx[i], v.y = ty[i], B = tbox[i];
+    c = near_square(sq, B, troot[i], t, coarse);
   }
-  walk_near(x, y, B, root, t, v);
-  out[(int64_t)r * ldy + tidx[i]] = scale * v.f;
+  leaf[sq][lane] = coarse ? c : -1;
+  __syncthreads();
+  if (c >= 0 && coarse) {  // a coarser leaf on several squares is the first one's
+    bool dup = false;
+    for (int k = 0; k < sq; ++k) dup = dup || leaf[k][lane] == c;
+    if (!dup) v.direct(c);
+  }
+  if (c >= 0 && !coarse) walk_subtree(v.x, v.y, c, t, v);
+  if (sq == 4 && B >= 0 && t.lev[B] >= 2) {
+    const double ir = 1.0 / t.rad[B];
+    const cx<double> w{(v.x - t.cx[B]) * ir, (v.y - t.cy[B]) * ir};
+    v.f += series_at<P>(L + ((int64_t)r * nbox + B) * P, w).x;
+  }
+  part[sq][lane] = v.f;
+  __syncthreads();
+  if (sq == 0 && on) {
+    double f = 0.0;
+#pragma unroll
+    for (int k = 0; k < kEvSquares; ++k) f += part[k][lane];
+    out[(int64_t)r * ldy + tidx[i]] = scale * f;
+  }
 }
 
 // ---------------------------------------------- sources at arbitrary points
@@ -409,8 +454,8 @@ void launch_eval_points(int P, int64_t n, const double *tx, const double *ty, co
   const auto *Lc = (const cx<double> *)L;
 #define LBS_EVAL_POINTS(PP)                                                                     \
   case PP:                                                                                      \
-    hipLaunchKernelGGL((k_eval_points<PP>), grid, dim3(64), 0, s, n, tx, ty, tbox, troot, tidx, \
-                       t, pc, pl.ns, Mc, Lc, pl.nbox, out, ldy, scale);                         \
+    hipLaunchKernelGGL((k_eval_points<PP>), grid, dim3(64 * kEvSquares), 0, s, n, tx, ty, tbox, \
+                       troot, tidx, t, pc, pl.ns, Mc, Lc, pl.nbox, out, ldy, scale);            \
     break;
   switch (P) {
     LBS_EVAL_POINTS(20)
