@@ -401,9 +401,8 @@ __global__ void __launch_bounds__(256)
     sc[i][c] = m0 + i < M ? cxyz[3 * (m0 + i) + c] : 0.0;
   }
   __syncthreads();
-  double acc[kTIsl], ws = 0.0;
-#pragma unroll
-  for (int i = 0; i < kTIsl; ++i) acc[i] = 0.0;
+  LogSum acc[kTIsl];
+  double ws = 0.0;
   const int64_t t0 = (int64_t)ch * kTTgt;
   for (int j = 0; j < kTTgt / 256; ++j) {
     const int64_t t = t0 + tid + 256 * j;
@@ -413,12 +412,12 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int i = 0; i < kTIsl; ++i) {
       const double d0 = x0 - sc[i][0], d1 = x1 - sc[i][1], d2 = x2 - sc[i][2];
-      acc[i] += wt * log(d0 * d0 + d1 * d1 + d2 * d2);
+      acc[i].add(wt, d0 * d0 + d1 * d1 + d2 * d2);
     }
   }
 #pragma unroll
   for (int i = 0; i < kTIsl; ++i) {
-    const double v = wsum(acc[i]);
+    const double v = wsum(acc[i].value());
     if (ln == 0) red[wv][i] = v;
   }
   {

@@ -205,12 +205,14 @@ __global__ void __launch_bounds__(256)
     for (int l = P - 1; l >= 0; --l) s = cfma(s, u, cx<double>{L[2 * l], L[2 * l + 1]});
     double tot = s.x - 0.5 * L[2 * (P + 1)] * elll[i];
     const double x0 = xyz[3 * i], x1 = xyz[3 * i + 1], x2 = xyz[3 * i + 2];
+    LogSum near;
     for (int e = e0; e < e1; ++e) {
       const int m = near_idx[e];
       const double d0 = x0 - cxyz[3 * m], d1 = x1 - cxyz[3 * m + 1],
                    d2 = x2 - cxyz[3 * m + 2];
-      tot += zr[m] * 0.5 * log(d0 * d0 + d1 * d1 + d2 * d2);
+      near.add(0.5 * zr[m], d0 * d0 + d1 * d1 + d2 * d2);
     }
+    tot += near.value();
     const double ez = -kInvPi * tot + kLog2 * 0.5 * kInvPi * L[2 * (P + 1) + 1];
     const double o = out[(int64_t)r * ldo + i] + alpha * ez;
     out[(int64_t)r * ldo + i] = add ? add[(int64_t)r * ldo + i] + o : o;
@@ -391,15 +393,16 @@ __global__ void k_build_schur(const int32_t *__restrict__ isl_geo,
   }
   const int m = gisl[g] + ml;
   const double c0 = cxyz[3 * m], c1 = cxyz[3 * m + 1], c2 = cxyz[3 * m + 2];
-  double acc = 0.0;
+  LogSum acc;
   const int64_t n = offs[k + 1] - offs[k];
+#pragma unroll 2
   for (int64_t i = offs[k]; i < offs[k + 1]; ++i) {
     const double d0 = xyz[3 * i] - c0, d1 = xyz[3 * i + 1] - c1,
                  d2 = xyz[3 * i + 2] - c2;
-    acc += log(d0 * d0 + d1 * d1 + d2 * d2);
+    acc.add(1.0, d0 * d0 + d1 * d1 + d2 * d2);
   }
   // 2 G = -(1/2pi) log|d|^2 + log2 / 2pi
-  const double sum2g = -0.5 * kInvPi * acc + 0.5 * kInvPi * kLog2 * (double)n;
+  const double sum2g = -0.5 * kInvPi * acc.value() + 0.5 * kInvPi * kLog2 * (double)n;
   Sg[(int64_t)kl * Mg + ml] = -sum2g;
 }
 
@@ -1199,16 +1202,17 @@ __global__ void __launch_bounds__(256)
   if (t >= T) return;
   const int g = tgeo ? tgeo[t] : 0;
   const double x0 = txyz[3 * t], x1 = txyz[3 * t + 1], x2 = txyz[3 * t + 2];
-  double acc = 0.0, asum = 0.0;
+  LogSum acc;
+  double asum = 0.0;
   const double *Ar = A + (int64_t)r * lda;
   for (int m = gisl[g]; m < gisl[g + 1]; ++m) {
     const double d0 = x0 - cxyz[3 * m], d1 = x1 - cxyz[3 * m + 1],
                  d2 = x2 - cxyz[3 * m + 2];
-    acc += Ar[m] * log(d0 * d0 + d1 * d1 + d2 * d2);
+    acc.add(Ar[m], d0 * d0 + d1 * d1 + d2 * d2);
     asum += Ar[m];
   }
   // G = -(1/4pi) log|d|^2 + log2/4pi
-  u[(int64_t)r * ldu + t] += -0.25 * kInvPi * acc +
+  u[(int64_t)r * ldu + t] += -0.25 * kInvPi * acc.value() +
                              0.25 * kInvPi * kLog2 * asum + add[r * G + g];
 }
 
@@ -1233,13 +1237,20 @@ __global__ void __launch_bounds__(256)
   const int64_t t = (int64_t)blockIdx.x * 256 + tid;
   if (t >= T) return;
   const double x0 = txyz[3 * t], x1 = txyz[3 * t + 1], x2 = txyz[3 * t + 2];
-  double acc = 0.0;
-  for (int j = 0; j < nm; ++j) {
-    const double4 c = sc[j];
+  LogSum acc[2];  // even and odd islands
+  for (int j = 0; j + 1 < nm; j += 2)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double4 c = sc[j + h];
+      const double d0 = x0 - c.x, d1 = x1 - c.y, d2 = x2 - c.z;
+      acc[h].add(c.w, d0 * d0 + d1 * d1 + d2 * d2);
+    }
+  if (nm & 1) {
+    const double4 c = sc[nm - 1];
     const double d0 = x0 - c.x, d1 = x1 - c.y, d2 = x2 - c.z;
-    acc += c.w * log(d0 * d0 + d1 * d1 + d2 * d2);
+    acc[0].add(c.w, d0 * d0 + d1 * d1 + d2 * d2);
   }
-  part[((int64_t)r * nch + ch) * T + t] = acc;
+  part[((int64_t)r * nch + ch) * T + t] = acc[0].value() + acc[1].value();
 }
 
 __global__ void __launch_bounds__(256)

@@ -7,6 +7,7 @@
 // fraction of one FMM application.
 #include <cmath>
 
+#include "cplx.h"
 #include "lbs_internal.h"
 
 namespace lbs {
@@ -34,7 +35,8 @@ __global__ void __launch_bounds__(256)
     x1 = x[3 * i + 1];
     x2 = x[3 * i + 2];
   }
-  double acc = 0.0, gsum = 0.0;
+  LogSum acc;
+  double gsum = 0.0;
   for (int j0 = 0; j0 < nv; j0 += 256) {
     __syncthreads();
     const int jl = j0 + threadIdx.x;
@@ -48,13 +50,13 @@ __global__ void __launch_bounds__(256)
     const int jn = min(256, nv - j0);
     for (int jj = 0; jj < jn; ++jj) {
       const double d0 = x0 - vx[jj], d1 = x1 - vy[jj], d2 = x2 - vz[jj];
-      acc += vg[jj] * log(d0 * d0 + d1 * d1 + d2 * d2);
+      acc.add(vg[jj], d0 * d0 + d1 * d1 + d2 * d2);
       gsum += vg[jj];
     }
   }
   if (!live) return;
   // G = -(1/4 pi) log|x - v|^2 + (1/4 pi) log 2
-  const double f = kInv4Pi * (kLog2v * gsum - acc);
+  const double f = kInv4Pi * (kLog2v * gsum - acc.value());
   const double base = in ? beta * in[(int64_t)r * ldi + i] : 0.0;
   out[(int64_t)r * ldo + i] = base + alpha * f;
 }
