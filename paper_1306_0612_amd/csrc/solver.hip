@@ -64,12 +64,20 @@ __device__ __forceinline__ bool in_sorted(const int32_t *a, int n, int x) {
 
 // L_k for every island k from its far list (Geometry::far_*: the pairs,
 // q = rho'_k / eta' and log|c_k - c_m|, sorted by |q|, largest first).
-// One wave per (island, half of the series): half h sums the terms
+// One work-group per (island, half of the series): half h sums the terms
 // h P/2 + 1 .. (h + 1) P/2 of every chunk whose |q| needs them, starting
 // from z q^(h P/2 + 1) by repeated squaring; half 0 also forms L0, Z_far
 // and Z_total.  A chunk needs the terms that keep the series tail below
-// the bound of the full P terms at the far limit |q| = 1/3.
-__global__ void __launch_bounds__(64)
+// the bound of the full P terms at the far limit |q| = 1/3.  The chunks are
+// dealt to the waves in turn, so that each has its share of the long series.
+//
+// Bound by reading the lists (28 bytes a pair: 24 us for 2000 islands) and,
+// with few waves in flight, by their latency and that of the sums over the
+// lanes: 32 shuffles instead of 192 by exchanging halves.
+// 2000 islands: 52 us with one wave and plain sums, now 43; 16 geometries,
+// eight columns: 74 us, now 28.
+constexpr int kLogWaves = 2;  // at most
+__global__ void __launch_bounds__(64 * kLogWaves)
     k_logsrc_local(int M, const int32_t *__restrict__ isl_geo,
                    const int32_t *__restrict__ gisl,
                    const int64_t *__restrict__ far_ptr,
@@ -82,29 +90,30 @@ __global__ void __launch_bounds__(64)
                    double *__restrict__ Lout) {
   constexpr int P = kPlog, PH = P / 2, stride = log_stride<P>();
   static_assert(2 * PH == P, "the series splits in two halves");
+  static_assert(2 * PH + 2 <= 32, "one value per lane pair");
+  __shared__ double part[kLogWaves][33];
   const int k = blockIdx.x, r = blockIdx.y, h = blockIdx.z;
-  const int ln = threadIdx.x;
+  const int ln = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int l0 = h * PH;  // this half: powers l0 + 1 .. l0 + PH
   const double *zr = z + (int64_t)r * ldz;
   double *out = Lout + ((int64_t)r * M + k) * stride;
   const int64_t e0 = far_ptr[k], e1 = far_ptr[k + 1];
   const int32_t *ntc = far_nt + far_cptr[k];
   if (h > 0 && (e1 == e0 || ntc[0] <= l0)) {  // no chunk reaches this half
-    if (ln < PH) {
-      out[2 * (l0 + ln + 1)] = 0.0;
-      out[2 * (l0 + ln + 1) + 1] = 0.0;
+    if (threadIdx.x < PH) {
+      out[2 * (l0 + threadIdx.x + 1)] = 0.0;
+      out[2 * (l0 + threadIdx.x + 1) + 1] = 0.0;
     }
     return;
   }
-  cx<double> acc[PH];
+  double v[32];  // the series' real and imaginary parts, then L0 and Z_far
 #pragma unroll
-  for (int l = 0; l < PH; ++l) acc[l] = cx<double>{0.0, 0.0};
-  double a0 = 0.0, zf = 0.0;
+  for (int l = 0; l < 32; ++l) v[l] = 0.0;
   const int nch = (int)((e1 - e0 + kLogChunk - 1) / kLogChunk);
   // U chunks per step, their loads issued before any of them is used (4:
   // few enough registers for four waves per SIMD)
   constexpr int U = 4;
-  for (int c0 = 0; c0 < nch; c0 += U) {
+  for (int c0 = wv; c0 < nch; c0 += U * nw) {
     int nt[U];
     cx<double> q[U];
     double hh[U], zm[U];
@@ -112,10 +121,11 @@ __global__ void __launch_bounds__(64)
     for (int u = 0; u < U; ++u) {
       // indices clamped into the list (nch >= 1 here); entries past the
       // end or of chunks without terms for this half get zero weight
-      const int64_t j = e0 + (int64_t)(c0 + u) * kLogChunk + ln;
+      const int c = c0 + u * nw;
+      const int64_t j = e0 + (int64_t)c * kLogChunk + ln;
       const int64_t jc = j < e1 ? j : e1 - 1;
-      const int nc = ntc[c0 + u < nch ? c0 + u : nch - 1] - l0;
-      nt[u] = c0 + u < nch ? nc : 0;  // wave-uniform
+      const int nc = ntc[c < nch ? c : nch - 1] - l0;
+      nt[u] = c < nch ? nc : 0;  // wave-uniform
       const bool ok = nt[u] > 0 && j < e1;
       const int mi = far_idx[jc];
       const cx<double> qi{far_q[2 * jc], far_q[2 * jc + 1]};
@@ -129,8 +139,8 @@ __global__ void __launch_bounds__(64)
       if (nt[u] <= 0) continue;  // wave-uniform
       cx<double> pw = zm[u] * q[u];
       if (h == 0) {
-        zf += zm[u];
-        a0 += zm[u] * hh[u];
+        v[2 * PH] += zm[u] * hh[u];
+        v[2 * PH + 1] += zm[u];
       } else {
         cx<double> base = q[u];
         for (int p = l0; p > 0; p >>= 1) {
@@ -141,35 +151,45 @@ __global__ void __launch_bounds__(64)
 #pragma unroll
       for (int l = 0; l < PH; ++l) {
         if (l < nt[u]) {
-          acc[l] = acc[l] + pw;
+          v[2 * l] += pw.x;
+          v[2 * l + 1] += pw.y;
           pw = pw * q[u];
         }
       }
     }
     if (nt[U - 1] <= 0) break;  // later chunks need no more terms
   }
+  // sums over the lanes: at each step a lane gives half of its values away
+  // and adds the partner's other half; lane ln ends with value ln / 2
 #pragma unroll
-  for (int l = 0; l < PH; ++l) {
-    const double sc = -1.0 / (double)(l0 + l + 1);  // -q^l / l
-    const double vx = wave_sum(acc[l].x), vy = wave_sum(acc[l].y);
-    if (ln == 0) {
-      out[2 * (l0 + l + 1)] = vx * sc;
-      out[2 * (l0 + l + 1) + 1] = vy * sc;
+  for (int n = 16, o = 32; n > 0; n >>= 1, o >>= 1) {
+    const bool up = ln & o;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const double give = up ? v[i] : v[i + n], keep = up ? v[i + n] : v[i];
+      v[i] = keep + __shfl_xor(give, o, 64);
     }
   }
+  v[0] += __shfl_xor(v[0], 1, 64);
+  if ((ln & 1) == 0) part[wv][ln >> 1] = v[0];
   if (h == 0) {
     double zt = 0.0;
     const int g = isl_geo[k];
-    for (int m = gisl[g] + ln; m < gisl[g + 1]; m += 64) zt += zr[m];
-    a0 = wave_sum(a0);
-    zf = wave_sum(zf);
+    for (int m = gisl[g] + (int)threadIdx.x; m < gisl[g + 1]; m += (int)blockDim.x) zt += zr[m];
     zt = wave_sum(zt);
-    if (ln == 0) {
-      out[0] = a0;
-      out[1] = 0.0;
-      out[2 * (P + 1)] = zf;
-      out[2 * (P + 1) + 1] = zt;
-    }
+    if (ln == 0) part[wv][32] = zt;
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t > 32) return;
+  double f = 0.0;
+  if (t < 32 || h == 0)
+    for (int w = 0; w < nw; ++w) f += part[w][t];
+  if (t < 2 * PH) out[2 * (l0 + 1) + t] = f * (-1.0 / (double)(l0 + t / 2 + 1));  // -q^l / l
+  else if (h == 0) {
+    if (t == 2 * PH) out[0] = f, out[1] = 0.0;
+    if (t == 2 * PH + 1) out[2 * (P + 1)] = f;
+    if (t == 32) out[2 * (P + 1) + 1] = f;
   }
 }
 
@@ -307,7 +327,11 @@ void launch_logsrc_apply(const Geometry &g, Workspace &ws, const double *z,
                          int64_t ldz, int nrhs, double *out, int64_t ldo,
                          double alpha, hipStream_t s, const double *add) {
   if (g.M == 0 || g.N == 0) return;
-  hipLaunchKernelGGL(k_logsrc_local, dim3(g.M, nrhs, 2), dim3(64), 0, s, g.M,
+  // a second wave once a list takes more than one step of a wave (4 chunks):
+  // 2000 islands 58 -> 43 us, 300: 9.8 -> 8.1; with lists of one or two
+  // chunks it has nothing to do (16 geometries, eight columns: 28 -> 42)
+  const int nw = g.maxM > 4 * kLogChunk ? kLogWaves : 1;
+  hipLaunchKernelGGL(k_logsrc_local, dim3(g.M, nrhs, 2), dim3(64 * nw), 0, s, g.M,
                      g.isl_geo.p, g.dgisl.p, g.far_ptr.p, g.far_cptr.p,
                      g.far_nt.p, g.far_idx.p, g.far_q.p, g.far_h.p, z, ldz,
                      ws.logL.p);
