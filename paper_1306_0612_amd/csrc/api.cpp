@@ -489,12 +489,14 @@ struct lbs_ctx {
   DBuf<int32_t> cg_ptr, cg_isl;
   DBuf<double> cg_zone;
   int32_t *count_host = nullptr;
+  uint64_t *word_host = nullptr;  // GMRES: iteration and active systems (k_gs_givens)
   // pinned staging for target coordinates read back to the host
   double *stage_host = nullptr;
   size_t stage_n = 0;
   DBuf<int32_t> diff;  // device flag of the target comparison
   ~lbs_ctx() {
     if (count_host) (void)hipHostFree(count_host);
+    if (word_host) (void)hipHostFree(word_host);
     if (stage_host) (void)hipHostFree(stage_host);
   }
 };
@@ -627,8 +629,8 @@ void ensure_gmres(lbs_ctx &c, int R) {
   st.active.alloc(S);
   st.kused.alloc(S);
   st.count.alloc(1);
-  st.tally.alloc(2);
-  LBS_HIP(hipMemset(st.tally.p, 0, 2 * sizeof(int32_t)));
+  st.tally.alloc(3);
+  LBS_HIP(hipMemset(st.tally.p, 0, 3 * sizeof(int32_t)));
   st.part1.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
   st.part2.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
   st.bvec.alloc((size_t)R * n);
@@ -642,6 +644,25 @@ int read_count(lbs_ctx &c, hipStream_t s) {
                          hipMemcpyDeviceToHost, s));
   LBS_HIP(hipStreamSynchronize(s));
   return *c.count_host;
+}
+
+// The number of systems active after iteration `it` of a cycle, as
+// k_gs_givens writes it to host memory.  A stream that has run dry or failed
+// without that write ends the wait.
+int wait_count(lbs_ctx &c, uint32_t it, hipStream_t s) {
+  for (uint32_t spin = 1;; ++spin) {
+    const uint64_t w = __atomic_load_n(c.word_host, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(w >> 32) == it) return (int)(uint32_t)w;
+    if (spin % 4096 == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) continue;
+      LBS_HIP(e);
+      const uint64_t last = __atomic_load_n(c.word_host, __ATOMIC_ACQUIRE);
+      if ((uint32_t)(last >> 32) == it) return (int)(uint32_t)last;
+      fail(LBS_ERR_HIP, "GMRES: the stream ended without the iteration's result");
+    }
+    __builtin_ia32_pause();
+  }
 }
 
 struct GmresOut {
@@ -670,8 +691,7 @@ std::vector<const void *> graph_signature(lbs_ctx &c) {
 // x = 0.  Classical Gram-Schmidt with `passes` passes (2: CGS2; 1 serves
 // the inner solves of mixed-precision refinement, which stop at a loose
 // tolerance and whose errors the FP64 outer residual corrects), Givens
-// rotations, one 4-byte read of the number of active systems per
-// iteration.  With graph_id >= 0 (and graphs enabled, stage timing off)
+// rotations, one wait per iteration for the number of active systems.  With graph_id >= 0 (and graphs enabled, stage timing off)
 // the body of iteration k is captured once as a HIP graph under the key
 // (graph_id, R, k) and replayed afterwards; a graph_id always comes with
 // the same number of passes.
@@ -706,6 +726,7 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
   while (true) {
     launch_segdots(c.seg_sys, R, 1, V, 0, n, V, n, st.nrm2.p, c.ws.red.p, s);
     launch_fill_int(1, 0, st.count.p, s);
+    launch_fill_int(1, 0, st.tally.p + 2, s);  // iterations of this cycle
     launch_gmres_start(S, m, st.nrm2.p, st.tol.p, st.gv.p, st.active.p,
                        st.kused.p, st.count.p, s);
     if (read_count(c, s) == 0) {
@@ -713,6 +734,7 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
       return out;
     }
     if (out.iters >= max_iter) return out;
+    *c.word_host = 0;  // the stream is idle here
     launch_normalize_seg(n, R, G, rg, st.nrm2.p, st.active.p, V, V, s);
     int alive = 1;
     int kc = 0;
@@ -730,7 +752,7 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
                          passes > 1 ? st.h2.p : st.h1.p, false, np, q);
         launch_gs_givens(c.seg_gs, S, k, m, np, st.h1.p, passes > 1 ? st.h2.p : nullptr,
                          st.nrm2.p, st.tol.p, st.H.p, st.cs.p, st.sn.p, st.gv.p, st.resid.p,
-                         st.active.p, st.kused.p, st.tally.p, st.count.p, q);
+                         st.active.p, st.kused.p, st.tally.p, c.word_host, q);
         launch_normalize_seg(n, R, G, rg, st.nrm2.p, st.active.p, w, w, q);
       };
       if (use_graphs) {
@@ -757,7 +779,7 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
       } else {
         body(s);
       }
-      alive = read_count(c, s);
+      alive = wait_count(c, (uint32_t)k + 1, s);
       ++out.iters;
       kc = k + 1;
       if (alive == 0 || out.iters >= max_iter) break;
@@ -1590,6 +1612,8 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
   }
   ensure_ws(*ctx, 1);
   LBS_HIP(hipHostMalloc((void **)&ctx->count_host, 2 * sizeof(int32_t), hipHostMallocDefault));
+  LBS_HIP(hipHostMalloc((void **)&ctx->word_host, sizeof(uint64_t),
+                        hipHostMallocMapped | hipHostMallocCoherent));
   LBS_HIP(hipStreamSynchronize(s));
   return ctx.release();
 }

@@ -540,7 +540,7 @@ void launch_gmres_start(int S, int m, const double *nrm2, const double *tol,
 void launch_gs_givens(const SegPlan &sp, int S, int k, int m, const double *npart,
                       const double *h1, const double *h2, double *nrm2, const double *tol,
                       double *H, double *cs, double *sn, double *g, double *resid,
-                      int32_t *active, int32_t *kused, int32_t *tally, int32_t *count,
+                      int32_t *active, int32_t *kused, int32_t *tally, uint64_t *word,
                       hipStream_t s);
 void launch_backsolve_seg(int S, int m, const double *H, const double *g,
                           const int32_t *kused, double *y, hipStream_t s);
