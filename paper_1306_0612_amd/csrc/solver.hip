@@ -1806,29 +1806,48 @@ void launch_gs_givens(const SegPlan &sp, int S, int k, int m, const double *npar
   LBS_HIP(hipGetLastError());
 }
 
-// y[s] = R_s^{-1} g_s over the first kused[s] columns (zeros beyond).
-__global__ void k_backsolve_seg(int S, int m, const double *__restrict__ H,
-                                const double *__restrict__ g,
-                                const int32_t *__restrict__ kused,
-                                double *__restrict__ y) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+// y[s] = R_s^{-1} g_s over the first kused[s] columns (zeros beyond), one
+// wave per system: lane i holds rows i and i + 64 (m <= 120), and column j
+// leaves the rows above it once y_j is known, eight columns' loads in flight.
+// A chain of k divisions: 34 columns take 5 us against 55 with one thread
+// per system, which waited for each entry of R in turn.
+__global__ void __launch_bounds__(256)
+    k_backsolve_seg(int S, int m, const double *__restrict__ H, const double *__restrict__ g,
+                    const int32_t *__restrict__ kused, double *__restrict__ y) {
+  const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (s >= S) return;
   const double *Hs = H + (int64_t)s * (m + 1) * m;
   const double *gs = g + (int64_t)s * (m + 1);
   double *ys = y + (int64_t)s * m;
-  const int k = kused[s];
-  for (int i = m - 1; i >= k; --i) ys[i] = 0.0;
-  for (int i = k - 1; i >= 0; --i) {
-    double acc = gs[i];
-    for (int j = i + 1; j < k; ++j) acc -= Hs[(int64_t)j * (m + 1) + i] * ys[j];
-    const double d = Hs[(int64_t)i * (m + 1) + i];
-    ys[i] = d != 0.0 ? acc / d : 0.0;
+  const int k = kused[s], r0 = min(lane, m), r1 = min(lane + 64, m);
+  double a0 = gs[r0], a1 = gs[r1];
+  constexpr int U = 8;
+  for (int j0 = k - 1; j0 >= 0; j0 -= U) {
+    double c0[U], c1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double *col = Hs + (int64_t)max(j0 - u, 0) * (m + 1);
+      c0[u] = col[r0];
+      c1[u] = col[r1];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 - u;
+      if (j < 0) break;  // wave-uniform
+      const double d = __shfl(j < 64 ? c0[u] : c1[u], j & 63, 64);
+      const double v = __shfl(j < 64 ? a0 : a1, j & 63, 64);
+      const double yj = d != 0.0 ? v / d : 0.0;
+      a0 = lane < j ? a0 - c0[u] * yj : lane == j ? yj : a0;
+      a1 = lane + 64 < j ? a1 - c1[u] * yj : lane + 64 == j ? yj : a1;
+    }
   }
+  if (lane < m) ys[lane] = lane < k ? a0 : 0.0;
+  if (lane + 64 < m) ys[lane + 64] = lane + 64 < k ? a1 : 0.0;
 }
 
 void launch_backsolve_seg(int S, int m, const double *H, const double *g,
                           const int32_t *kused, double *y, hipStream_t s) {
-  hipLaunchKernelGGL(k_backsolve_seg, dim3((S + 63) / 64), dim3(64), 0, s, S,
+  hipLaunchKernelGGL(k_backsolve_seg, dim3((S + 3) / 4), dim3(256), 0, s, S,
                      m, H, g, kused, y);
   LBS_HIP(hipGetLastError());
 }
