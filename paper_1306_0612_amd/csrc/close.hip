@@ -38,8 +38,8 @@ __device__ __forceinline__ double wsum(double v) {
   return v;
 }
 
-// V for nodes kBvNodes blockIdx.z .. of island act[blockIdx.x], column
-// blockIdx.y.  Lane l of every wave holds nodes l and l + 64 of the tile;
+// V for the nodes of island act[blockIdx.x], column blockIdx.y, in tiles of
+// kBvNodes dealt over blockIdx.z.  Lane l of every wave holds nodes l and l + 64 of the tile;
 // the island's nodes j pass through LDS in tiles of 256, of which each wave
 // takes a quarter, and the waves' sums meet in LDS.  The differentiation
 // weights depend on i - j alone: 383 of them per pair of tiles, formed once
@@ -57,79 +57,83 @@ __global__ void __launch_bounds__(256)
   __shared__ double2 tz[kBvTile], td[kBvTile];  // xi_j, xi'_j
   __shared__ double ts[kBvTile];                // sigma_j
   __shared__ double wt[kBvNodes + kBvTile];     // weight of i - j
-  const int k = act[blockIdx.x], r = blockIdx.y, i0 = kBvNodes * (int)blockIdx.z;
+  const int k = act[blockIdx.x], r = blockIdx.y;
   const int64_t a = offs[k];
   const int n = (int)(offs[k + 1] - a);
-  if (i0 >= n) return;  // block-uniform
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double h = kTwoPi / (double)n;
   const double *sg = sigma + (int64_t)r * ldx + a;
   const bool even = (n & 1) == 0;
-  double si[2], xr[2], xm[2], ds[2], vr[2], vi[2];
+  for (int64_t ib = kBvNodes * (int64_t)blockIdx.z; ib < n; ib += kBvNodes * (int64_t)gridDim.z) {
+    const int i0 = (int)ib;
+    double si[2], xr[2], xm[2], ds[2], vr[2], vi[2];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int i = min(i0 + lane + 64 * q, n - 1);
-    si[q] = sg[i];
-    xr[q] = xi[2 * (a + i)];
-    xm[q] = xi[2 * (a + i) + 1];
-    ds[q] = 0.0;           // spectral derivative of sigma at node i
-    vr[q] = vi[q] = 0.0;   // sum of (sigma_j - sigma_i) xi'_j / (xi_j - xi_i)
-  }
-  for (int j0 = 0; j0 < n; j0 += kBvTile) {
-    __syncthreads();
-    const int jl = j0 + tid;
-    const bool in = jl < n;  // past the end: sigma and xi' zero, weight below
-    ts[tid] = in ? sg[jl] : 0.0;
-    tz[tid] = in ? make_double2(xi[2 * (a + jl)], xi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
-    td[tid] = in ? make_double2(dxi[2 * (a + jl)], dxi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
-    for (int x = tid; x < kBvNodes + kBvTile; x += 256) {
-      const int m = i0 - j0 + x - (kBvTile - 1);  // i - j
-      double w = 0.0;
-      if (m != 0 && m > -n && m < n) {
-        double sn, cs;
-        sincospi((double)m / (double)n, &sn, &cs);
-        w = ((m & 1) ? -0.5 : 0.5) * (even ? cs / sn : 1.0 / sn);
-      }
-      wt[x] = w;
+    for (int q = 0; q < 2; ++q) {
+      const int i = min(i0 + lane + 64 * q, n - 1);
+      si[q] = sg[i];
+      xr[q] = xi[2 * (a + i)];
+      xm[q] = xi[2 * (a + i) + 1];
+      ds[q] = 0.0;           // spectral derivative of sigma at node i
+      vr[q] = vi[q] = 0.0;   // sum of (sigma_j - sigma_i) xi'_j / (xi_j - xi_i)
     }
-    __syncthreads();
-    const int ja = wv * (kBvTile / 4), jb = min(ja + kBvTile / 4, n - j0);
+    for (int j0 = 0; j0 < n; j0 += kBvTile) {
+      __syncthreads();
+      const int jl = j0 + tid;
+      const bool in = jl < n;  // past the end: sigma and xi' zero, weight below
+      ts[tid] = in ? sg[jl] : 0.0;
+      tz[tid] = in ? make_double2(xi[2 * (a + jl)], xi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
+      td[tid] =
+          in ? make_double2(dxi[2 * (a + jl)], dxi[2 * (a + jl) + 1]) : make_double2(0.0, 0.0);
+      for (int x = tid; x < kBvNodes + kBvTile; x += 256) {
+        const int m = i0 - j0 + x - (kBvTile - 1);  // i - j
+        double w = 0.0;
+        if (m != 0 && m > -n && m < n) {
+          double sn, cs;
+          sincospi((double)m / (double)n, &sn, &cs);
+          w = ((m & 1) ? -0.5 : 0.5) * (even ? cs / sn : 1.0 / sn);
+        }
+        wt[x] = w;
+      }
+      __syncthreads();
+      const int ja = wv * (kBvTile / 4), jb = min(ja + kBvTile / 4, n - j0);
 #pragma unroll 2
-    for (int jj = ja; jj < jb; ++jj) {
-      const double2 z = tz[jj], d = td[jj];
-      const double sj = ts[jj];
+      for (int jj = ja; jj < jb; ++jj) {
+        const double2 z = tz[jj], d = td[jj];
+        const double sj = ts[jj];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        ds[q] += wt[lane + 64 * q + kBvTile - 1 - jj] * sj;
-        const double dx = z.x - xr[q], dy = z.y - xm[q];
-        // (a node's own term: sigma_j - sigma_i = 0 times a finite value)
-        const double d2 = fma(dx, dx, fma(dy, dy, 1e-300));
-        const double rc = __builtin_amdgcn_rcp(d2), e = fma(-d2, rc, 1.0);
-        const double g = (sj - si[q]) * fma(rc, fma(e, e, e), rc);
-        // dxi_j / (xi_j - xi_i) = dxi_j * conj(d) / |d|^2
-        vr[q] += g * fma(d.x, dx, d.y * dy);
-        vi[q] += g * fma(d.y, dx, -(d.x * dy));
+        for (int q = 0; q < 2; ++q) {
+          ds[q] += wt[lane + 64 * q + kBvTile - 1 - jj] * sj;
+          const double dx = z.x - xr[q], dy = z.y - xm[q];
+          // (a node's own term: sigma_j - sigma_i = 0 times a finite value)
+          const double d2 = fma(dx, dx, fma(dy, dy, 1e-300));
+          const double rc = __builtin_amdgcn_rcp(d2), e = fma(-d2, rc, 1.0);
+          const double g = (sj - si[q]) * fma(rc, fma(e, e, e), rc);
+          // dxi_j / (xi_j - xi_i) = dxi_j * conj(d) / |d|^2
+          vr[q] += g * fma(d.x, dx, d.y * dy);
+          vi[q] += g * fma(d.y, dx, -(d.x * dy));
+        }
       }
     }
-  }
-  // the four waves' sums: [value][wave][lane], in the tile buffers
-  __syncthreads();
-  double *red = reinterpret_cast<double *>(tz);  // 4 kBvTile doubles: 4 waves x 64 x (ds + vr, vi)
+    // the four waves' sums: [value][wave][lane], in the tile buffers
+    __syncthreads();
+    // 4 kBvTile doubles: 4 waves x 64 x (ds + vr, vi)
+    double *red = reinterpret_cast<double *>(tz);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    red[wv * 64 + lane] = vr[q] + ds[q];
-    red[256 + wv * 64 + lane] = vi[q];
-    __syncthreads();
-    const int i = i0 + lane + 64 * q;
-    if (wv == 0 && i < n) {
-      const double sr = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
-      const double sm = (red[256 + lane] + red[320 + lane]) + (red[384 + lane] + red[448 + lane]);
-      // V = h (sum + ds) / (2 pi i) = -i h (sum + ds) / (2 pi)
-      const double f = h / kTwoPi;
-      V[2 * ((int64_t)r * ldv + a + i)] = f * sm;
-      V[2 * ((int64_t)r * ldv + a + i) + 1] = -f * sr;
+    for (int q = 0; q < 2; ++q) {
+      red[wv * 64 + lane] = vr[q] + ds[q];
+      red[256 + wv * 64 + lane] = vi[q];
+      __syncthreads();
+      const int i = i0 + lane + 64 * q;
+      if (wv == 0 && i < n) {
+        const double sr = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
+        const double sm = (red[256 + lane] + red[320 + lane]) + (red[384 + lane] + red[448 + lane]);
+        // V = h (sum + ds) / (2 pi i) = -i h (sum + ds) / (2 pi)
+        const double f = h / kTwoPi;
+        V[2 * ((int64_t)r * ldv + a + i)] = f * sm;
+        V[2 * ((int64_t)r * ldv + a + i) + 1] = -f * sr;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -200,7 +204,8 @@ void launch_close_eval(const Geometry &g, const ClosePlan &cp, int nrhs,
   if (cp.n_tgt == 0) return;
   int maxn = 0;
   for (int32_t v : g.nodes) maxn = std::max(maxn, (int)v);
-  hipLaunchKernelGGL(k_close_bvals, dim3(cp.n_act, nrhs, (maxn + kBvNodes - 1) / kBvNodes),
+  const unsigned gz = (unsigned)std::min<int64_t>(((int64_t)maxn + kBvNodes - 1) / kBvNodes, 32768);
+  hipLaunchKernelGGL(k_close_bvals, dim3(cp.n_act, nrhs, gz),
                      dim3(256), 0, s,
                      cp.act.p, g.doffs.p, g.xi.p, g.dxi.p, sigma, ldx, V, g.N);
   hipLaunchKernelGGL(k_close_correct, dim3((cp.n_tgt + 3) / 4, nrhs),
