@@ -1330,6 +1330,7 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
   for (int k = 0; k < M; ++k) {
     if (nodes[k] < 8) fail(LBS_ERR_INVALID_ARG, "island " + std::to_string(k) + ": fewer than 8 nodes");
     g.offs[k + 1] = g.offs[k] + nodes[k];
+    g.maxn = std::max(g.maxn, (int)nodes[k]);
   }
   std::vector<lbs_island> smp_isl;
   if (sm) {

@@ -202,9 +202,7 @@ void launch_close_eval(const Geometry &g, const ClosePlan &cp, int nrhs,
                        const double *sigma, int64_t ldx, double *V,
                        double *u, int64_t ldu, hipStream_t s) {
   if (cp.n_tgt == 0) return;
-  int maxn = 0;
-  for (int32_t v : g.nodes) maxn = std::max(maxn, (int)v);
-  const unsigned gz = (unsigned)std::min<int64_t>(((int64_t)maxn + kBvNodes - 1) / kBvNodes, 32768);
+  const unsigned gz = (unsigned)std::min((g.maxn - 1) / kBvNodes + 1, 32768);
   hipLaunchKernelGGL(k_close_bvals, dim3(cp.n_act, nrhs, gz),
                      dim3(256), 0, s,
                      cp.act.p, g.doffs.p, g.xi.p, g.dxi.p, sigma, ldx, V, g.N);

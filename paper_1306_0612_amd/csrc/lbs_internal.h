@@ -248,6 +248,7 @@ struct Geometry {
   int M = 0;
   int G = 1;
   int maxM = 0;                      // largest island count of a geometry
+  int maxn = 0;                      // largest node count of an island
   std::vector<int32_t> nodes;        // per island
   std::vector<int64_t> offs;         // node offset per island (M+1)
   std::vector<int64_t> gnode;        // node offset per geometry (G+1)

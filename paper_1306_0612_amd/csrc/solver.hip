@@ -195,9 +195,12 @@ __global__ void __launch_bounds__(64 * kLogWaves)
 
 // (E z)_i: the island's expansion at u = xi'_i / rho'_k (all P terms; the
 // coefficients beyond those its far list needs are zero), plus its near
-// centres directly.  One work-group per (island, right-hand side): the
-// island's coefficients and near centres are the same for every lane, so
-// they are read with scalar loads.
+// centres directly.  Work-groups of 256 nodes of one island and right-hand
+// side (blockIdx.z): the island's coefficients and near centres are the
+// same for every lane, so they are read with scalar loads.  Bound by HBM
+// (72 B a node) where there are many islands, by the series' chain where
+// there are few: 5.4 us for 40 curves of about 400 nodes, 8.1 with all of an
+// island's nodes in one work-group.
 __global__ void __launch_bounds__(256)
     k_logsrc_node(int M, const int64_t *__restrict__ offs,
                   const double *__restrict__ xil,
@@ -218,7 +221,8 @@ __global__ void __launch_bounds__(256)
   const double *zr = z + (int64_t)r * ldz;
   const int e0 = near_ptr[k], e1 = near_ptr[k + 1];
   const int64_t i1 = offs[k + 1];
-  for (int64_t i = offs[k] + threadIdx.x; i < i1; i += 256) {
+  for (int64_t i = offs[k] + 256 * (int64_t)blockIdx.z + threadIdx.x; i < i1;
+       i += 256 * (int64_t)gridDim.z) {
     const cx<double> u{xil[2 * i] * ir, xil[2 * i + 1] * ir};
     cx<double> s{L[2 * P], L[2 * P + 1]};
 #pragma unroll
@@ -237,7 +241,7 @@ __global__ void __launch_bounds__(256)
     const double o = out[(int64_t)r * ldo + i] + alpha * ez;
     out[(int64_t)r * ldo + i] = add ? add[(int64_t)r * ldo + i] + o : o;
   }
-  if (add && threadIdx.x == 0) {  // the island's own row, behind the node rows
+  if (add && blockIdx.z == 0 && threadIdx.x == 0) {  // the island's own row, behind the node rows
     const int64_t i = (int64_t)r * ldo + offs[M] + k;
     out[i] = add[i] + zr[k];
   }
@@ -335,7 +339,12 @@ void launch_logsrc_apply(const Geometry &g, Workspace &ws, const double *z,
                      g.isl_geo.p, g.dgisl.p, g.far_ptr.p, g.far_cptr.p,
                      g.far_nt.p, g.far_idx.p, g.far_q.p, g.far_h.p, z, ldz,
                      ws.logL.p);
-  hipLaunchKernelGGL(k_logsrc_node, dim3(g.M, nrhs), dim3(256), 0, s, g.M,
+  // more work-groups per island while its first ones leave the chip idle (40
+  // islands 8.1 -> 5.4 us; 16 geometries x 8 columns 48 -> 53, 2000 islands
+  // 23.5 either way)
+  const bool few = (int64_t)g.M * nrhs < 1024;
+  const unsigned gz = few ? (unsigned)std::min((g.maxn - 1) / 256 + 1, 32768) : 1u;
+  hipLaunchKernelGGL(k_logsrc_node, dim3(g.M, nrhs, gz), dim3(256), 0, s, g.M,
                      g.doffs.p, g.xil.p, g.xyz.p, g.elll.p, g.rhol.p,
                      g.dcenter.p, g.nearR_ptr.p, g.nearR_idx.p, z, ldz,
                      ws.logL.p, out, ldo, alpha, add);
