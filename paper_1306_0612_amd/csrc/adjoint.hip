@@ -157,7 +157,8 @@ void launch_dl_strengths(const Geometry &g, const double *sigma, double *out,
 // (l = 1..P), slot 2 P holds Y_k and slot 2 P + 1 ELL_k.  One wave per
 // (island, half of the series): half h sums the powers h P/2 + 1 .. (h + 1)
 // P/2, starting from u^(h P/2 + 1) by repeated squaring; half 0 also forms
-// Y_k and ELL_k.
+// Y_k and ELL_k.  Bound by latency: the 32 sums over the lanes took most of
+// 9.7 us at 40 x 200 nodes one value at a time, 5.2 by exchanging halves.
 __global__ void __launch_bounds__(64)
     k_island_moments(int M, const int64_t *__restrict__ offs,
                      const double *__restrict__ xil,
@@ -169,17 +170,17 @@ __global__ void __launch_bounds__(64)
   const int k = blockIdx.x, h = blockIdx.y, ln = threadIdx.x;
   const int l0 = h * PH;
   const double ir = 1.0 / rhol[k];
-  cx<double> acc[PH];
+  static_assert(2 * PH + 2 <= 32, "one value per lane pair");
+  double v[32];  // the powers' real and imaginary parts, then Y_k and ELL_k
 #pragma unroll
-  for (int l = 0; l < PH; ++l) acc[l] = cx<double>{0.0, 0.0};
-  double ys = 0.0, ys_ell = 0.0;
+  for (int l = 0; l < 32; ++l) v[l] = 0.0;
   for (int64_t i = offs[k] + ln; i < offs[k + 1]; i += 64) {
     const double yi = y[i];
     const cx<double> u{xil[2 * i] * ir, xil[2 * i + 1] * ir};
     cx<double> pw = yi * u;
     if (h == 0) {
-      ys += yi;
-      ys_ell += yi * elll[i];
+      v[2 * PH] += yi;
+      v[2 * PH + 1] += yi * elll[i];
     } else {
       cx<double> base = u;  // pw = y_i u^(l0 + 1)
       for (int e = l0; e > 0; e >>= 1) {
@@ -189,27 +190,16 @@ __global__ void __launch_bounds__(64)
     }
 #pragma unroll
     for (int l = 0; l < PH; ++l) {
-      acc[l] = acc[l] + pw;
+      v[2 * l] += pw.x;
+      v[2 * l + 1] += pw.y;
       pw = pw * u;
     }
   }
-#pragma unroll
-  for (int l = 0; l < PH; ++l) {
-    const double inv = 1.0 / (double)(l0 + l + 1);
-    const double vx = wsum(acc[l].x), vy = wsum(acc[l].y);
-    if (ln == 0) {
-      mom[(int64_t)(2 * (l0 + l)) * M + k] = vx * inv;
-      mom[(int64_t)(2 * (l0 + l) + 1) * M + k] = vy * inv;
-    }
-  }
-  if (h == 0) {
-    ys = wsum(ys);
-    ys_ell = wsum(ys_ell);
-    if (ln == 0) {
-      mom[(int64_t)(2 * P) * M + k] = ys;
-      mom[(int64_t)(2 * P + 1) * M + k] = ys_ell;
-    }
-  }
+  const double sum = lane_sums32(v, ln);
+  const int t = ln >> 1;
+  if (ln & 1) return;
+  if (t < 2 * PH) mom[(int64_t)(2 * l0 + t) * M + k] = sum * (1.0 / (double)(l0 + t / 2 + 1));
+  else if (h == 0) mom[(int64_t)(2 * P + t - 2 * PH) * M + k] = sum;
 }
 
 // (E^T y)_m for a tile of TM consecutive centres m per block: threads over
@@ -346,11 +336,15 @@ void launch_logsrc_T(const Geometry &g, const double *y, double *mom,
   if (g.M == 0) return;
   hipLaunchKernelGGL(k_island_moments, dim3(g.M, 2), dim3(64), 0, s, g.M,
                      g.doffs.p, g.xil.p, g.elll.p, g.rhol.p, y, mom);
-  constexpr int TM = 4;
-  hipLaunchKernelGGL(k_logsrc_T<TM>, dim3((g.M + TM - 1) / TM), dim3(256), 0, s,
-                     g.M, g.isl_geo.p, g.dgisl.p, g.doffs.p, g.dcenter.p,
-                     g.xyz.p, g.nearRT_ptr.p, g.nearRT_idx.p, g.frame.p, g.rhol.p, mom, y,
-                     alpha, out);
+  // four centres per work-group share the moments' reads where that leaves a
+  // work-group per CU; fewer islands get a work-group per centre, as a
+  // group's centres take their near sums one after another (40 islands:
+  // 16.4 us four to a work-group, 7.0 one)
+  const bool few = g.M < 1024;
+  const int tm = few ? 1 : 4;
+  hipLaunchKernelGGL(few ? k_logsrc_T<1> : k_logsrc_T<4>, dim3((g.M + tm - 1) / tm), dim3(256), 0,
+                     s, g.M, g.isl_geo.p, g.dgisl.p, g.doffs.p, g.dcenter.p, g.xyz.p,
+                     g.nearRT_ptr.p, g.nearRT_idx.p, g.frame.p, g.rhol.p, mom, y, alpha, out);
   LBS_HIP(hipGetLastError());
 }
 

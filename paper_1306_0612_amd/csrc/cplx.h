@@ -92,4 +92,20 @@ struct LogSum {
   }
 };
 
+// Sums of 32 values over the 64 lanes: at each step a lane gives half of its
+// values away and adds the partner's other half (32 shuffles; 192 one value
+// at a time); lanes 2 i and 2 i + 1 return value i's sum.
+// (N: values kept; a recursion, so that every index is static)
+template <int N = 16>
+__device__ __forceinline__ double lane_sums32(double (&v)[32], int lane) {
+  const bool up = lane & (2 * N);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double give = up ? v[i] : v[i + N], keep = up ? v[i + N] : v[i];
+    v[i] = keep + __shfl_xor(give, 2 * N, 64);
+  }
+  if constexpr (N > 1) return lane_sums32<N / 2>(v, lane);
+  else return v[0] + __shfl_xor(v[0], 1, 64);
+}
+
 }  // namespace lbs

@@ -159,19 +159,8 @@ __global__ void __launch_bounds__(64 * kLogWaves)
     }
     if (nt[U - 1] <= 0) break;  // later chunks need no more terms
   }
-  // sums over the lanes: at each step a lane gives half of its values away
-  // and adds the partner's other half; lane ln ends with value ln / 2
-#pragma unroll
-  for (int n = 16, o = 32; n > 0; n >>= 1, o >>= 1) {
-    const bool up = ln & o;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-      const double give = up ? v[i] : v[i + n], keep = up ? v[i + n] : v[i];
-      v[i] = keep + __shfl_xor(give, o, 64);
-    }
-  }
-  v[0] += __shfl_xor(v[0], 1, 64);
-  if ((ln & 1) == 0) part[wv][ln >> 1] = v[0];
+  const double sum = lane_sums32(v, ln);
+  if ((ln & 1) == 0) part[wv][ln >> 1] = sum;
   if (h == 0) {
     double zt = 0.0;
     const int g = isl_geo[k];
