@@ -422,9 +422,11 @@ struct EvalPlan {
   DBuf<int64_t> didx;           // transposed: idx on the device
   DBuf<int32_t> dtgeo;
   // forward, targets located in the handle's own tree (no tree of their
-  // own): sorted by the deepest box holding them, with that box (-1:
-  // outside the root square), their tree's root and their API index
+  // own): sorted by the deepest box holding them, with that box (-1: the
+  // root or outside its square; the first `lone` targets), their tree's root
+  // and their API index
   bool located = false;
+  int64_t lone = 0;
   DBuf<double> ltx, lty;
   DBuf<int32_t> lbox, lroot;
   DBuf<int64_t> lidx;
@@ -1698,8 +1700,9 @@ EvalPlan &eval_plan(lbs_ctx &c, bool transposed, const std::vector<int64_t> &tof
     ep->lbox.alloc((size_t)n);
     ep->lroot.alloc((size_t)n);
     ep->lidx.alloc((size_t)n);
-    launch_locate_targets(n, dtx.p, dty.p, ep->didx.p, G > 1 ? ep->dtgeo.p : nullptr, c.plan,
-                          ep->ltx.p, ep->lty.p, ep->lbox.p, ep->lroot.p, ep->lidx.p, s);
+    ep->lone = launch_locate_targets(n, dtx.p, dty.p, ep->didx.p, G > 1 ? ep->dtgeo.p : nullptr,
+                                     c.plan, ep->ltx.p, ep->lty.p, ep->lbox.p, ep->lroot.p,
+                                     ep->lidx.p, s);
     if (transposed) {
       build_point_sources(c.plan, n, ep->ltx.p, ep->lty.p, ep->lbox.p, ep->lroot.p, ep->src, s);
       ep->located_src = true;
@@ -1808,8 +1811,8 @@ void eval_impl(lbs_ctx &c, int nrhs, const double *sigma, const double *A,
         throw;
       }
       c.ws.timer = keep;
-      launch_eval_points(c.tab64.P, (int64_t)ep.idx.size(), ep.ltx.p, ep.lty.p, ep.lbox.p,
-                         ep.lroot.p, ep.lidx.p, c.plan, c.ws.pstr64.p, c.ws.mult64.p,
+      launch_eval_points(c.tab64.P, (int64_t)ep.idx.size(), ep.lone, ep.ltx.p, ep.lty.p,
+                         ep.lbox.p, ep.lroot.p, ep.lidx.p, c.plan, c.ws.pstr64.p, c.ws.mult64.p,
                          c.ws.loc64.p, nrhs, u, T, 0.5, s);
     } else {
       ep.ws.ensure(ep.pl, c.opt.p64, c.opt.p32, nrhs, g.N, g.M, G, kPlog);

@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(256)
   if (i >= n) return;
   const int r = roots[tgeo ? tgeo[idx[i]] : 0];
   const int b = descend(tx[i], ty[i], r, 1 << 30, cxv, cyv, rad, lev, child0, nchild, leaf);
-  keys[i] = (uint64_t)(b + 1);
+  keys[i] = b >= 0 && lev[b] > 0 ? (uint64_t)(b + 1) : 0;  // (the root has no neighbourhood)
   vals[i] = (int32_t)i;
 }
 
@@ -82,9 +82,11 @@ __global__ void __launch_bounds__(256)
                      const double *__restrict__ ty, const int64_t *__restrict__ idx,
                      const int32_t *__restrict__ tgeo, const int32_t *__restrict__ roots,
                      double *__restrict__ ox, double *__restrict__ oy, int32_t *__restrict__ obox,
-                     int32_t *__restrict__ oroot, int64_t *__restrict__ oidx) {
+                     int32_t *__restrict__ oroot, int64_t *__restrict__ oidx,
+                     int64_t *__restrict__ lone) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
+  if (keys[j] == 0 && (j + 1 == n || keys[j + 1] != 0)) *lone = j + 1;
   const int i = vals[j];
   ox[j] = tx[i];
   oy[j] = ty[i];
@@ -226,57 +228,60 @@ struct SumVisitor {
   __device__ void direct(int b) { f += direct_sum(x, y, t.s0[b], t.s1[b], t.sx, t.sy, p); }
 };
 
-// Nine waves per 64 targets (sorted by their box), right-hand side
-// blockIdx.y: wave o takes square o of the 3 x 3 neighbourhood of its
-// targets' boxes (wave 4 the local expansions as well), and
-// out[r ldy + idx] = scale Re Psi(z) sums the nine.  Bound by the latency of
-// the walks (dependent loads of box data): one thread per target walked the
-// nine squares in turn, each found from the root, on 1.5 waves per SIMD at
-// 1e5 targets (0.84 ms over 1M nodes; the nine waves 0.45 ms).  Nine lanes
-// of one wave per target take as long there, but twice as long at 4e5
-// targets of a small problem: neighbouring targets of one box walk the same
-// boxes, and a wave of one square keeps their lanes together.
+// Targets sorted by their box, right-hand side blockIdx.y:
+// out[r ldy + idx] = scale Re Psi(z).  W = 9: nine waves per 64 targets, wave
+// o takes square o of the 3 x 3 neighbourhood of its targets' boxes (wave 4
+// the local expansions as well), and the nine are summed.  Nine lanes of one
+// wave per target take twice as long at 4e5 targets of a small problem:
+// neighbouring targets of one box walk the same boxes, and a wave of one
+// square keeps their lanes together.  W = 1: one thread per target walks the
+// squares in turn.  Bound by the latency of the walks (dependent loads of box
+// data).
 constexpr int kEvSquares = 9;
-template <int P>
-__global__ void __launch_bounds__(64 * kEvSquares)
+template <int P, int W>
+__global__ void __launch_bounds__(64 * W)
     k_eval_points(int64_t n, const double *__restrict__ tx, const double *__restrict__ ty,
                   const int32_t *__restrict__ tbox, const int32_t *__restrict__ troot,
                   const int64_t *__restrict__ tidx, TreeView t, const cx<double> *__restrict__ p,
                   int64_t ns, const cx<double> *__restrict__ M, const cx<double> *__restrict__ L,
                   int nbox, double *__restrict__ out, int64_t ldy, double scale) {
-  __shared__ int leaf[kEvSquares][64];
-  __shared__ double part[kEvSquares][64];
-  const int lane = threadIdx.x & 63, sq = threadIdx.x >> 6, r = blockIdx.y;
+  static_assert(W == 1 || W == kEvSquares, "all squares or one a wave");
+  const int lane = threadIdx.x & 63, sq = W == 1 ? 4 : threadIdx.x >> 6, r = blockIdx.y;
   const int64_t i = (int64_t)blockIdx.x * 64 + lane;
   const bool on = i < n;
   SumVisitor<P> v{0.0, 0.0, 0.0, t, p + (int64_t)r * ns, M + (int64_t)r * nbox * P};
-  int B = -1, c = -1;
-  bool coarse = false;
-  if (on) {
-    v.x = tx[i], v.y = ty[i], B = tbox[i];
-    c = near_square(sq, B, troot[i], t, coarse);
+  int B = -1, root = 0;
+  if (on) v.x = tx[i], v.y = ty[i], B = tbox[i], root = troot[i];
+  if constexpr (W == 1) {
+    if (on) walk_near(v.x, v.y, B, root, t, v);
+  } else {
+    __shared__ int leaf[W][64];
+    bool coarse = false;
+    const int c = on ? near_square(sq, B, root, t, coarse) : -1;
+    leaf[sq][lane] = coarse ? c : -1;
+    __syncthreads();
+    if (c >= 0 && coarse) {  // a coarser leaf on several squares is the first one's
+      bool dup = false;
+      for (int k = 0; k < sq; ++k) dup = dup || leaf[k][lane] == c;
+      if (!dup) v.direct(c);
+    }
+    if (c >= 0 && !coarse) walk_subtree(v.x, v.y, c, t, v);
   }
-  leaf[sq][lane] = coarse ? c : -1;
-  __syncthreads();
-  if (c >= 0 && coarse) {  // a coarser leaf on several squares is the first one's
-    bool dup = false;
-    for (int k = 0; k < sq; ++k) dup = dup || leaf[k][lane] == c;
-    if (!dup) v.direct(c);
-  }
-  if (c >= 0 && !coarse) walk_subtree(v.x, v.y, c, t, v);
   if (sq == 4 && B >= 0 && t.lev[B] >= 2) {
     const double ir = 1.0 / t.rad[B];
     const cx<double> w{(v.x - t.cx[B]) * ir, (v.y - t.cy[B]) * ir};
     v.f += series_at<P>(L + ((int64_t)r * nbox + B) * P, w).x;
   }
-  part[sq][lane] = v.f;
-  __syncthreads();
-  if (sq == 0 && on) {
-    double f = 0.0;
+  if constexpr (W > 1) {
+    __shared__ double part[W][64];
+    part[sq][lane] = v.f;
+    __syncthreads();
+    if (sq != 0) return;
+    v.f = 0.0;
 #pragma unroll
-    for (int k = 0; k < kEvSquares; ++k) f += part[k][lane];
-    out[(int64_t)r * ldy + tidx[i]] = scale * f;
+    for (int k = 0; k < W; ++k) v.f += part[k][lane];
   }
+  if (on) out[(int64_t)r * ldy + tidx[i]] = scale * v.f;
 }
 
 // ---------------------------------------------- sources at arbitrary points
@@ -419,15 +424,18 @@ __global__ void __launch_bounds__(256)
 
 }  // namespace
 
-void launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
-                           const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
-                           int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s) {
-  if (n <= 0) return;
+int64_t launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
+                              const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
+                              int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s) {
+  if (n <= 0) return 0;
   if (n >= (int64_t)INT32_MAX) throw ApiError{LBS_ERR_UNSUPPORTED, "more than 2^31 targets"};
   DBuf<uint64_t> keys;
   DBuf<int32_t> vals;
+  DBuf<int64_t> dl;
   keys.alloc((size_t)n);
   vals.alloc((size_t)n);
+  dl.alloc(1);
+  launch_fill_int(2, 0, reinterpret_cast<int32_t *>(dl.p), s);
   const unsigned g = (unsigned)((n + 255) / 256);
   hipLaunchKernelGGL(k_locate, dim3(g), dim3(256), 0, s, n, tx, ty, idx, tgeo, pl.roots.p,
                      pl.cx.p, pl.cy.p, pl.rad.p, pl.lev.p, pl.child0.p, pl.nchild.p, pl.leaf.p,
@@ -436,26 +444,47 @@ void launch_locate_targets(int64_t n, const double *tx, const double *ty, const 
   while ((1ll << bits) <= (int64_t)pl.nbox) ++bits;
   sort_by_key(keys.p, vals.p, n, bits, s);
   hipLaunchKernelGGL(k_gather_located, dim3(g), dim3(256), 0, s, n, keys.p, vals.p, tx, ty, idx,
-                     tgeo, pl.roots.p, ox, oy, obox, oroot, oidx);
+                     tgeo, pl.roots.p, ox, oy, obox, oroot, oidx, dl.p);
   LBS_HIP(hipGetLastError());
+  int64_t lone = 0;
+  LBS_HIP(hipMemcpyAsync(&lone, dl.p, sizeof(lone), hipMemcpyDeviceToHost, s));
   LBS_HIP(hipStreamSynchronize(s));  // keys, vals are released on return
+  return lone;
 }
 
-void launch_eval_points(int P, int64_t n, const double *tx, const double *ty, const int32_t *tbox,
-                        const int32_t *troot, const int64_t *tidx, const DevPlan &pl,
-                        const double *pstr, const double *M, const double *L, int nrhs,
-                        double *out, int64_t ldy, double scale, hipStream_t s) {
+void launch_eval_points(int P, int64_t n, int64_t lone, const double *tx, const double *ty,
+                        const int32_t *tbox, const int32_t *troot, const int64_t *tidx,
+                        const DevPlan &pl, const double *pstr, const double *M, const double *L,
+                        int nrhs, double *out, int64_t ldy, double scale, hipStream_t s) {
   if (n <= 0 || nrhs <= 0) return;
   const TreeView t{pl.cx.p, pl.cy.p, pl.rad.p, pl.lev.p, pl.parent.p, pl.child0.p, pl.nchild.p,
                    pl.leaf.p, pl.s0.p, pl.s1.p, pl.sx.p, pl.sy.p};
-  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)nrhs);
   const auto *pc = (const cx<double> *)pstr;
   const auto *Mc = (const cx<double> *)M;
   const auto *Lc = (const cx<double> *)L;
-#define LBS_EVAL_POINTS(PP)                                                                     \
-  case PP:                                                                                      \
-    hipLaunchKernelGGL((k_eval_points<PP>), grid, dim3(64 * kEvSquares), 0, s, n, tx, ty, tbox, \
-                       troot, tidx, t, pc, pl.ns, Mc, Lc, pl.nbox, out, ldy, scale);            \
+  // Nine waves share 64 targets while a thread each leaves the chip idle, at
+  // less than two waves per SIMD; above that the squares' unequal work costs
+  // more than it gains.  Nine / one, whole call: 46 waves 585 / 1003 us at 1M
+  // nodes and 185 / 292 at 8000, 1562 waves 1054 / 1106 and 300 / 280, 4686
+  // waves 2.76 / 2.55 ms and 620 / 470 us, 15625 waves 4.9 / 4.1 and 1.56 /
+  // 0.98 ms.  Of nine waves of targets without a neighbourhood eight have no
+  // work, so those take a thread each, in a launch of their own, from half a
+  // wave per SIMD on (1e5 targets, nearly all outside the square of one
+  // 4000-node curve: 353 us among the others, 220 so; 468 waves of 400 small
+  // islands' 212 and 231).
+  auto waves = [nrhs](int64_t k) { return (k + 63) / 64 * nrhs; };
+  const bool split = waves(n) < 2048;
+  const int64_t each = !split ? n : waves(lone) >= 512 ? lone : 0;
+  auto run = [&](auto kern, int W, int64_t a, int64_t k) {
+    if (k > 0)
+      hipLaunchKernelGGL(kern, dim3((unsigned)((k + 63) / 64), (unsigned)nrhs),
+                         dim3((unsigned)(64 * W)), 0, s, k, tx + a, ty + a, tbox + a, troot + a,
+                         tidx + a, t, pc, pl.ns, Mc, Lc, pl.nbox, out, ldy, scale);
+  };
+#define LBS_EVAL_POINTS(PP)                                          \
+  case PP:                                                           \
+    run(k_eval_points<PP, 1>, 1, 0, each);                           \
+    run(k_eval_points<PP, kEvSquares>, kEvSquares, each, n - each);  \
     break;
   switch (P) {
     LBS_EVAL_POINTS(20)

@@ -616,18 +616,20 @@ void sort_by_key(uint64_t *keys, int32_t *vals, int64_t n, int bits, SortBufs &s
                  hipStream_t s);
 // Targets located in a plan's tree (evalpts.hip): the n targets (tx, ty;
 // API index idx; geometry tgeo[idx] or 0) sorted by the deepest box whose
-// square holds them (-1 outside the root square), with their roots and
-// API indices.  The plan needs its tree links and roots on the device.
-void launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
-                           const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
-                           int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s);
+// square holds them (-1: the root or outside its square), with their roots
+// and API indices; returns the number of those with -1, which come first.
+// The plan needs its tree links and roots on the device.
+int64_t launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
+                              const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
+                              int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s);
 // out[r ldy + tidx[i]] = scale Re sum_j p_j / (z_i - z_j) for located
-// targets, from the plan's FP64 expansions M, L (order P) and strengths
-// pstr of its sources (far_field already run for the nrhs right-hand sides).
-void launch_eval_points(int P, int64_t n, const double *tx, const double *ty, const int32_t *tbox,
-                        const int32_t *troot, const int64_t *tidx, const DevPlan &pl,
-                        const double *pstr, const double *M, const double *L, int nrhs,
-                        double *out, int64_t ldy, double scale, hipStream_t s);
+// targets (the first `lone` of them at -1), from the plan's FP64 expansions
+// M, L (order P) and strengths pstr of its sources (far_field already run for
+// the nrhs right-hand sides).
+void launch_eval_points(int P, int64_t n, int64_t lone, const double *tx, const double *ty,
+                        const int32_t *tbox, const int32_t *troot, const int64_t *tidx,
+                        const DevPlan &pl, const double *pstr, const double *M, const double *L,
+                        int nrhs, double *out, int64_t ldy, double scale, hipStream_t s);
 void launch_copy_cols(int64_t n, int R, double a, const double *src, int64_t lds,
                       double *dst, int64_t ldd, hipStream_t s);
 void launch_scale_sqrt(int S, double t, const double *nrm2, double *out,
