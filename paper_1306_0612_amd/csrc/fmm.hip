@@ -1349,6 +1349,7 @@ __device__ __forceinline__ int pow2_at_least(int n) {
 }
 
 constexpr int kStage = 128;  // U-list sources staged in LDS per pass
+constexpr int kLeafSlices = 16;  // parts of a target one lane adds (FP64 leaf kernel)
 constexpr int kFarItems = 8;  // expansions staged in LDS per pass (FP64 leaf kernel)
 
 // What the FP64 leaf kernel forms at a target.
@@ -1567,22 +1568,37 @@ __global__ void __launch_bounds__(256, MODE == kLeafField && RB == 1 ? 6 : 3)
       }
     };
     // value c of every lane's targets through LDS: red[slice][target], the
-    // far parts behind them; lane t < nt adds its target's parts
+    // far parts behind them; lane t < nt adds its target's parts.  Of the
+    // complex fields more than kLeafSlices parts are added over the lanes of
+    // their wave first: one lane's chain over them, up to 256 for a leaf of
+    // one target and four waves, for each of two or four values, took longer
+    // than the sums (198 leaves of 4 targets 19.7 us, now 8.4; one value's
+    // chain, in kLeafField, is shorter than the shuffles)
     double tot[NF];
 #pragma unroll
     for (int c = 0; c < NF; ++c) tot[c] = 0.0;
     auto fin = [&](int c, int sl, int tl, int tp, int S, const auto &v, auto kk) {
       constexpr int K = decltype(kk)::value;
-      const int row = tp * K;
-      double *fr = sh + S * row;
+      constexpr bool fold = MODE != kLeafField;
+      const int row = tp * K, lane = tid & 63, wv = tid >> 6;
+      const bool near = fold && S > kLeafSlices, far_ = fold && Sf > kLeafSlices;  // block-uniform
+      const int ns = near ? W : S, nf = far_ ? W : Sf;
+      double *fr = sh + ns * row, ff = far[c];
+      if (far_)
+        for (int o = 1 << lgf; o < 64; o <<= 1) ff += __shfl_xor(ff, o, 64);
 #pragma unroll
-      for (int k = 0; k < K; ++k) sh[sl * row + k * tp + tl] = v[k];
-      fr[tid] = far[c];
+      for (int k = 0; k < K; ++k) {
+        double x = v[k];
+        if (near)
+          for (int o = tp; o < 64; o <<= 1) x += __shfl_xor(x, o, 64);
+        if (!near || lane < tp) sh[(near ? wv : sl) * row + k * tp + tl] = x;
+      }
+      if (!far_ || lane < 1 << lgf) fr[far_ ? (wv << lgf) + lane : tid] = ff;
       __syncthreads();
       if (tid < nt) {
         double s = 0.0;
-        for (int q = 0; q < Sf; ++q) s += fr[(q << lgf) + tid];
-        for (int q = 0; q < S; ++q) s += sh[q * row + tid];
+        for (int q = 0; q < nf; ++q) s += fr[(q << lgf) + tid];
+        for (int q = 0; q < ns; ++q) s += sh[q * row + tid];
         tot[c] = s;
       }
       __syncthreads();
