@@ -631,8 +631,7 @@ void ensure_gmres(lbs_ctx &c, int R) {
   st.active.alloc(S);
   st.kused.alloc(S);
   st.count.alloc(1);
-  st.tally.alloc(3);
-  LBS_HIP(hipMemset(st.tally.p, 0, 3 * sizeof(int32_t)));
+  st.tally.alloc(3);  // cleared by every cycle
   st.part1.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
   st.part2.alloc((size_t)(m + 1) * R * c.seg_gs.nchunk);
   st.bvec.alloc((size_t)R * n);
@@ -728,7 +727,7 @@ GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
   while (true) {
     launch_segdots(c.seg_sys, R, 1, V, 0, n, V, n, st.nrm2.p, c.ws.red.p, s);
     launch_fill_int(1, 0, st.count.p, s);
-    launch_fill_int(1, 0, st.tally.p + 2, s);  // iterations of this cycle
+    launch_fill_int(3, 0, st.tally.p, s);
     launch_gmres_start(S, m, st.nrm2.p, st.tol.p, st.gv.p, st.active.p,
                        st.kused.p, st.count.p, s);
     if (read_count(c, s) == 0) {

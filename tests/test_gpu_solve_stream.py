@@ -1,0 +1,70 @@
+"""Calls on a stream of their own while the device's null stream is busy:
+what they clear is cleared on their own stream, in order with its use (a
+clear on the null stream would come after it, or hold the call up)."""
+import time
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import nystrom
+from oracle.geometry import Curves
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def spin():
+    """Cycles of the spinning kernel (one wave) that take half a second."""
+    import torch
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    torch.cuda._sleep(1000000)
+    torch.cuda.synchronize()
+    return int(5e5 / (time.perf_counter() - t0))
+
+
+@pytest.fixture(scope="module")
+def problem():
+    isl = synth.star_islands(71, 3, (0.1, 0.2), nodes=64)
+    return isl, Curves(isl)
+
+
+def _busy(spin, call):
+    """call() on a side stream beside a spinning null stream; whether that
+    was still spinning at its end, and its result."""
+    import torch
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    done = torch.cuda.Event()
+    torch.cuda._sleep(spin)
+    done.record()
+    with torch.cuda.stream(side):
+        out = call()
+    side.synchronize()
+    still = not done.query()
+    torch.cuda.synchronize()
+    return still, out
+
+
+# eight systems take two work-groups of the step that counts them; a first
+# handle leaves its counters in memory that the second may get
+# Tolerance: GMRES to 1e-12 of the residual times the matrix' condition
+# number (2.8e3), and sqrt(195) from the 2-norm to the largest entry: 4e-8.
+def test_first_solve(spin, problem):
+    import torch
+    from paper_1306_0612_amd import lbs
+    isl, cv = problem
+    G = np.random.default_rng(72).normal(size=(8, cv.n))
+    A = nystrom.system_matrix(cv)
+    ref = np.linalg.solve(A, np.concatenate([2 * G, np.zeros((8, cv.m))], 1).T).T
+    g = torch.tensor(G.ravel(), device="cuda")
+    for _ in range(2):
+        sol = lbs.Solver([isl] * 8, graphs=0)
+        torch.cuda.synchronize()
+        still, (s, a, info) = _busy(spin, lambda: sol.solve(g, tol=1e-12, precision="fp64"))
+        assert still  # it did not wait for the null stream either
+        got = torch.cat([s.reshape(8, -1), a.reshape(8, -1)], 1).cpu().numpy()
+        assert np.abs(got - ref).max() < 4e-8 * np.abs(ref).max()
+        sol.close()
