@@ -368,7 +368,7 @@ void build_passes(DevPlan &pl, int p32, int p64, hipStream_t s, bool fp64_only =
 
 namespace lbs {
 void Workspace::ensure(const DevPlan &pl, int P64, int P32, int nrhs,
-                       int64_t N, int M, int G, int Plog) {
+                       int64_t N, int M, int G, int Plog, hipStream_t s) {
   if (nrhs <= nrhs_cap) return;
   nrhs_cap = nrhs;
   pstr64.alloc((size_t)pl.ns * nrhs * 2);
@@ -383,7 +383,7 @@ void Workspace::ensure(const DevPlan &pl, int P64, int P32, int nrhs,
     const int nch = (std::max(pl.n_leaf_s, 1) + 2047) / 2048;  // bound for every geometry
     gcsum.alloc((size_t)nch * G * nrhs);
     gcnt.alloc((size_t)G * nrhs);
-    LBS_HIP(hipMemset(gcnt.p, 0, gcnt.n * sizeof(int32_t)));
+    launch_fill_int((int64_t)gcnt.n, 0, gcnt.p, s);
   }
   tmpM.alloc((size_t)std::max(M, 1) * nrhs);
   logL.alloc((size_t)std::max(M, 1) * nrhs * (2 * (Plog + 1) + 2));
@@ -505,9 +505,9 @@ struct lbs_ctx {
 
 namespace {
 
-void ensure_ws(lbs_ctx &c, int nrhs) {
+void ensure_ws(lbs_ctx &c, int nrhs, hipStream_t s) {
   c.ws.ensure(c.plan, c.opt.p64, c.opt.p32, nrhs, c.geo.N, c.geo.M, c.geo.G,
-              kPlog);
+              kPlog, s);
 }
 
 // y = ident x + K x for the node rows (ld x / y given), with the FMM
@@ -550,7 +550,7 @@ void apply_K_ws(lbs_ctx &c, Workspace &w, int prec, int nrhs, const double *x, i
 
 void apply_K(lbs_ctx &c, int prec, int nrhs, const double *x, int64_t ldx,
              double *y, int64_t ldy, double ident, hipStream_t s) {
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   apply_K_ws(c, c.ws, prec, nrhs, x, ldx, y, ldy, ident, s);
 }
 
@@ -571,7 +571,7 @@ void apply_precond_op_ws(lbs_ctx &c, Workspace &w, int prec, int nrhs, const dou
 
 void apply_precond_op(lbs_ctx &c, int prec, int nrhs, const double *x,
                       double *y, hipStream_t s) {
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   apply_precond_op_ws(c, c.ws, prec, nrhs, x, y, s);
 }
 
@@ -591,7 +591,7 @@ void apply_system_ws(lbs_ctx &c, Workspace &w, int prec, int nrhs, const double 
 
 void apply_system(lbs_ctx &c, int prec, int nrhs, const double *x, double *y,
                   hipStream_t s) {
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   apply_system_ws(c, c.ws, prec, nrhs, x, y, s);
 }
 
@@ -600,7 +600,7 @@ void precond_rhs(lbs_ctx &c, int nrhs, const double *gdat, double *b,
                  hipStream_t s) {
   Geometry &g = c.geo;
   const int64_t n = g.N + g.M;
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   launch_copy_cols(g.N, nrhs, 2.0, gdat, g.N, b, n, s);
   launch_island_sums(g, b, n, nrhs, c.ws.tmpM.p, g.M, s);
   launch_gemv_blocks(g, c.ws.tmpM.p, g.M, nrhs, b + g.N, n, -1.0, s);
@@ -843,7 +843,7 @@ void system_rhs(lbs_ctx &c, int nrhs, const double *gdat, double *b, hipStream_t
 void apply_precond_inverse(lbs_ctx &c, int nrhs, double *x, hipStream_t s) {
   Geometry &g = c.geo;
   const int64_t n = g.N + g.M;
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   double *tmp = c.ws.tmpM.p;
   launch_island_sums(g, x, n, nrhs, tmp, g.M, s);
   for (int r = 0; r < nrhs; ++r)
@@ -1612,7 +1612,7 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
     ctx->sinv_info = invert_schur(g, S.p, g.Sinv.p, o.schur_tol, s);
     if (host_timing()) LBS_HIP(hipStreamSynchronize(s));
   }
-  ensure_ws(*ctx, 1);
+  ensure_ws(*ctx, 1, s);
   LBS_HIP(hipHostMalloc((void **)&ctx->count_host, 2 * sizeof(int32_t), hipHostMallocDefault));
   LBS_HIP(hipHostMalloc((void **)&ctx->word_host, sizeof(uint64_t),
                         hipHostMallocMapped | hipHostMallocCoherent));
@@ -1758,7 +1758,7 @@ EvalPlan &eval_plan(lbs_ctx &c, bool transposed, const std::vector<int64_t> &tof
       ep->qt.alloc(2 * g.N);
       launch_permute_complex(g.N, ep->pl.src_perm.p, g.qfac.p, ep->qt.p, s);
     }
-    ep->ws.ensure(ep->pl, c.opt.p64, c.opt.p32, 1, g.N, g.M, G, kPlog);
+    ep->ws.ensure(ep->pl, c.opt.p64, c.opt.p32, 1, g.N, g.M, G, kPlog, s);
     ep->tree = true;
   }
   if (c.opt.close_eval && n > 0) {
@@ -1800,7 +1800,7 @@ void eval_impl(lbs_ctx &c, int nrhs, const double *sigma, const double *A,
       LBS_HIP(hipStreamSynchronize(s));
     } else if (ep.located) {
       // the handle's own FP64 far field, then each target from its box
-      ensure_ws(c, nrhs);
+      ensure_ws(c, nrhs, s);
       StageTimer *keep = c.ws.timer;  // not one of the operator's stages
       c.ws.timer = nullptr;
       try {
@@ -1814,11 +1814,11 @@ void eval_impl(lbs_ctx &c, int nrhs, const double *sigma, const double *A,
                          ep.lbox.p, ep.lroot.p, ep.lidx.p, c.plan, c.ws.pstr64.p, c.ws.mult64.p,
                          c.ws.loc64.p, nrhs, u, T, 0.5, s);
     } else {
-      ep.ws.ensure(ep.pl, c.opt.p64, c.opt.p32, nrhs, g.N, g.M, G, kPlog);
+      ep.ws.ensure(ep.pl, c.opt.p64, c.opt.p32, nrhs, g.N, g.M, G, kPlog, s);
       fmm_apply64(ep.pl, c.tab64, ep.ws, ep.qt.p, sigma, g.N, nrhs, u, T, 0.5, Assembly{}, s);
     }
   }
-  ensure_ws(c, nrhs);
+  ensure_ws(c, nrhs, s);
   launch_segdots(c.seg_nodes, nrhs, 1, g.gw.p, 0, 0, sigma, g.N, c.ws.gam.p, c.ws.red.p, s);
   launch_axpby((int64_t)nrhs * G, 0.0, c.ws.gam.p, 0.5, c.ws.gam.p, s);
   launch_eval_logsrc(g, T, txyz, ep.dtgeo.p, A, g.M, nrhs, c.ws.gam.p, u, T, s, &ep.lpart);
@@ -2129,7 +2129,7 @@ lbs_status lbs_matvec(lbs_handle h, int32_t op, int32_t prec, int32_t nrhs, cons
     if (prec != LBS_FP64 && prec != LBS_MIXED) fail(LBS_ERR_INVALID_ARG, "bad precision");
     hipStream_t s = (hipStream_t)stream;
     lbs_ctx &c = *h;
-    ensure_ws(c, nrhs);
+    ensure_ws(c, nrhs, s);
     switch (op) {
       case LBS_OP_IPLUSK:
         apply_K(c, prec, nrhs, x, c.geo.N, y, c.geo.N, 1.0, s);
@@ -2170,7 +2170,7 @@ lbs_status lbs_solve(lbs_handle h, int32_t prec, int32_t nrhs, const double *gda
     const int64_t n = g.N + g.M;
     const bool pre = c.opt.precond != 0;
     auto t0 = std::chrono::steady_clock::now();
-    ensure_ws(c, R);
+    ensure_ws(c, R, s);
     ensure_gmres(c, R);
     GmresState &gm = c.gm;
     lbs_solve_info inf{};
@@ -2259,7 +2259,7 @@ lbs_status lbs_eval_T(lbs_handle h, int32_t nrhs, const double *w, int64_t T, co
       launch_fill((int64_t)g.M * nrhs, 0.0, ga, s);
       return;
     }
-    ensure_ws(c, 1);
+    ensure_ws(c, 1, s);
     ensure_adj(c);
     EvalPlan &ep = eval_plan(c, true, {0, T}, txyz, s);
     reject_close(ep, "lbs_eval_T");
@@ -2293,7 +2293,7 @@ lbs_status lbs_solve_T(lbs_handle h, int32_t prec, int32_t nrhs, const double *r
     const int R = nrhs, S = R * g.G;
     const int64_t n = g.N + g.M;
     auto t0 = std::chrono::steady_clock::now();
-    ensure_ws(c, R);
+    ensure_ws(c, R, s);
     ensure_gmres(c, R);
     ensure_adj(c);
     GmresState &gm = c.gm;
@@ -2348,7 +2348,7 @@ lbs_status lbs_shape_vjp(lbs_handle h, const double *sigma, const double *A, con
     if (!sigma || !A || !lam_s || !dcoef || (T > 0 && (!w || !txyz)))
       fail(LBS_ERR_INVALID_ARG, "null pointer argument");
     hipStream_t s = (hipStream_t)stream;
-    ensure_ws(c, 1);
+    ensure_ws(c, 1, s);
     ensure_adj(c);
     const int64_t N = g.N;
     DBuf<double> buf;
@@ -2417,7 +2417,7 @@ lbs_status lbs_set_orders(lbs_handle h, int32_t p64, int32_t p32, void *stream) 
     // expansion buffers are sized by the orders: reallocate on next use
     const int cap = std::max(1, c.ws.nrhs_cap);
     c.ws.nrhs_cap = 0;
-    ensure_ws(c, cap);
+    ensure_ws(c, cap, s);
     c.evf.reset();
     c.evt.reset();
     // captured iterations hold the old tables and kernels

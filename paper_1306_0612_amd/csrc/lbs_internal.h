@@ -340,7 +340,7 @@ struct Workspace {
   DBuf<double> red;       // reduction scratch
   DBuf<double> tmpM, logL;
   void ensure(const DevPlan &pl, int P64, int P32, int nrhs, int64_t N,
-              int M, int G, int Plog);
+              int M, int G, int Plog, hipStream_t s);
 };
 
 constexpr int kPlog = 30;  // terms of the per-island log-source expansions

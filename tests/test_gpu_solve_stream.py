@@ -68,3 +68,25 @@ def test_first_solve(spin, problem):
         got = torch.cat([s.reshape(8, -1), a.reshape(8, -1)], 1).cpu().numpy()
         assert np.abs(got - ref).max() < 4e-8 * np.abs(ref).max()
         sol.close()
+
+
+# Tolerances: those of the operator's parity tests, 1e-10 and 1e-6.
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-10), ("mixed", 1e-6)])
+def test_setup_and_first_product(spin, problem, prec, tol):
+    import torch
+    from paper_1306_0612_amd import lbs
+    isl, cv = problem
+    X = np.random.default_rng(73).normal(size=(2, cv.n))
+    ref = X @ (nystrom.kernel_block(cv, np.arange(cv.n)) + np.eye(cv.n)).T
+    x = torch.tensor(X, device="cuda")
+
+    def call():
+        sol = lbs.Solver(isl)
+        one = sol.matvec(x[0].contiguous(), "iplusk", prec)
+        return sol, one, sol.matvec(x, "iplusk", prec)  # two columns: larger buffers
+
+    for _ in range(2):
+        _, (sol, one, two) = _busy(spin, call)
+        for y, r in ((one, ref[0]), (two, ref)):
+            assert np.abs(y.cpu().numpy() - r).max() < tol * np.abs(r).max()
+        sol.close()
