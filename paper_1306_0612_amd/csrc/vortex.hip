@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(256)
     x1 = x[3 * i + 1];
     x2 = x[3 * i + 2];
   }
-  LogSum acc;
+  LogSums<true> acc;  // (positions are the caller's, not checked)
   double gsum = 0.0;
   for (int j0 = 0; j0 < nv; j0 += 256) {
     __syncthreads();
