@@ -252,11 +252,11 @@ void upload_plan(Tree &T, const double *sx, const double *sy,
     LBS_HIP(hipStreamSynchronize(s));  // rng, geo are released on return
   }
   pl.m2l_box.upload(m2l, s);
+  std::vector<int32_t> gp, xl;  // (until the wait at the end)
   {
     HostPhase ph("upload_plan M2L groups");
     // FP64 kernel: consecutive boxes in groups of at most kM2LEnt entries
     const int n = pl.n_m2l;
-    std::vector<int32_t> gp;
     int64_t ne = 0;
     int first = 0;
     for (int i = 0; i <= n; ++i) {
@@ -282,10 +282,8 @@ void upload_plan(Tree &T, const double *sx, const double *sy,
     }
     std::stable_sort(xb.begin(), xb.end(),
                      [](const auto &a, const auto &c) { return a.first < c.first; });
-    std::vector<int32_t> xl;
     for (const auto &x : xb) xl.push_back(x.second);
     pl.x_box.upload(xl, s);
-    LBS_HIP(hipStreamSynchronize(s));  // xl is released on return
   }
   auto points = [&](const std::vector<int64_t> &perm, const double *ax,
                     const double *ay, DBuf<double> &dx, DBuf<double> &dy) {
@@ -490,14 +488,15 @@ struct lbs_ctx {
   DBuf<uint64_t> cg_keys;
   DBuf<int32_t> cg_ptr, cg_isl;
   DBuf<double> cg_zone;
+  // pinned: GMRES' iteration and active systems (k_gs_givens), and the
+  // number of active systems at a cycle's start behind it
+  uint64_t *word_host = nullptr;
   int32_t *count_host = nullptr;
-  uint64_t *word_host = nullptr;  // GMRES: iteration and active systems (k_gs_givens)
   // pinned staging for target coordinates read back to the host
   double *stage_host = nullptr;
   size_t stage_n = 0;
   DBuf<int32_t> diff;  // device flag of the target comparison
   ~lbs_ctx() {
-    if (count_host) (void)hipHostFree(count_host);
     if (word_host) (void)hipHostFree(word_host);
     if (stage_host) (void)hipHostFree(stage_host);
   }
@@ -1613,9 +1612,9 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
     if (host_timing()) LBS_HIP(hipStreamSynchronize(s));
   }
   ensure_ws(*ctx, 1, s);
-  LBS_HIP(hipHostMalloc((void **)&ctx->count_host, 2 * sizeof(int32_t), hipHostMallocDefault));
-  LBS_HIP(hipHostMalloc((void **)&ctx->word_host, sizeof(uint64_t),
+  LBS_HIP(hipHostMalloc((void **)&ctx->word_host, 128 + 2 * sizeof(int32_t),
                         hipHostMallocMapped | hipHostMallocCoherent));
+  ctx->count_host = reinterpret_cast<int32_t *>(ctx->word_host + 16);
   LBS_HIP(hipStreamSynchronize(s));
   return ctx.release();
 }

@@ -610,15 +610,13 @@ __global__ void __launch_bounds__(64)
 void build_m2l_groups(DevPlan &pl, const std::vector<int32_t> &grp, hipStream_t s) {
   pl.n_grp = (int)(grp.size() / 2);
   if (pl.n_grp == 0) return;
-  DBuf<int32_t> dg;
-  dg.upload(grp, s);
+  pl.grp.upload(grp, s);
   pl.grp_ent.alloc((size_t)pl.n_grp * kM2LEnt);
   pl.grp_box.alloc((size_t)pl.n_grp * kM2LBoxes);
   hipLaunchKernelGGL(k_m2l_pack, dim3(pl.n_grp), dim3(64), 0, s,
-                     reinterpret_cast<const int2 *>(dg.p), pl.m2l_box.p, pl.v_ptr.p, pl.v_src.p,
+                     reinterpret_cast<const int2 *>(pl.grp.p), pl.m2l_box.p, pl.v_ptr.p, pl.v_src.p,
                      pl.v_code.p, pl.xf_ptr.p, pl.grp_ent.p, pl.grp_box.p);
   LBS_HIP(hipGetLastError());
-  LBS_HIP(hipStreamSynchronize(s));  // dg is released on return
 }
 
 // P2L sums of two boxes with X lists per wave (entries 2 e and 2 e + 1 of

@@ -153,6 +153,7 @@ struct DevPlan {
   // groups of M2L boxes of the FP64 kernel (build_m2l_groups): their V-list
   // entries and boxes
   int n_grp = 0;
+  DBuf<int32_t> grp;  // their first and number of m2l_box entries
   DBuf<int2> grp_ent, grp_box;
   DBuf<int32_t> x_box;  // boxes with X lists, most sources first
   // Upward (M2M) and downward (L2L) pass programs (PassProgram in tree.h)
@@ -169,8 +170,8 @@ struct DevPlan {
   Tree host;                                  // host tree (statistics)
 };
 
-// The FP64 M2L groups of a plan from (first entry of m2l_box, count) pairs
-// (fmm.hip).
+// The FP64 M2L groups of a plan from (first entry of m2l_box, count) pairs,
+// which the caller keeps until the stream has passed this (fmm.hip).
 void build_m2l_groups(DevPlan &pl, const std::vector<int32_t> &grp, hipStream_t s);
 
 // Translation tables for expansions of P terms (see fmm.hip).
