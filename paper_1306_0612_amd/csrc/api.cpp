@@ -218,6 +218,7 @@ void upload_plan(Tree &T, const double *sx, const double *sy,
       h.nt = T.t1[b] - T.t0[b];
       h.uf0 = ufp[b];
       h.uf1 = ufp[b + 1];
+      pl.max_u = std::max(pl.max_u, (int)(h.uf1 - h.uf0));
       h.wb = T.w_ptr[b];
       h.we = T.w_ptr[b + 1];
       h.b = b;

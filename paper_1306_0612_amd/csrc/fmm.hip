@@ -1643,7 +1643,11 @@ __global__ void __launch_bounds__(256, MODE == kLeafField && RB == 1 ? 6 : 3)
 // 31920 leaves, 62 / 58 / - at 11164, 43 / 28 / 33 at 3351, 31 / 20 / 18 at
 // 822; the complex fields, with more work per pair, gain from a second wave
 // only below 8192 leaves (transposed application 216 / 229 us at 11164).
-static int leaf64_waves(int64_t groups, bool field) {
+// Where no leaf has more sources (max_u) than one wave stages at a time and
+// there is a leaf per SIMD, more waves share only the staging: 1000 caps of 64
+// nodes, application of one / two waves 47.9 / 50.6 us, transposed 26.0 / 30.2.
+static int leaf64_waves(int64_t groups, bool field, int max_u) {
+  if (groups >= 1024 && max_u <= kStage) return 1;
   return groups >= (field ? 16384 : 8192) ? 1 : groups >= 2048 ? 2 : 4;
 }
 
@@ -1657,7 +1661,7 @@ static void launch_leaf64(const DevPlan &pl, const int64_t *ufp, const int32_t *
   if (pl.n_leaf_t == 0) return;
   const int ry = (nrhs + RB - 1) / RB;
   const int64_t groups = (int64_t)pl.n_leaf_t * ry;
-  const int W = leaf64_waves(groups, MODE == kLeafField);
+  const int W = leaf64_waves(groups, MODE == kLeafField, ufp ? INT32_MAX : pl.max_u);
   const size_t stage = (size_t)kStage * std::min(W, 2) * (1 + RB) * sizeof(double2);
   const size_t red = (size_t)(256 + 64) * W * sizeof(double);
   const size_t fari = kFarItems * (sizeof(double4) + P * sizeof(cx<double>));

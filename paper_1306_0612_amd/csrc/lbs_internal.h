@@ -122,6 +122,7 @@ constexpr int kM2LBoxes = 16, kM2LEnt = 64;
 
 struct DevPlan {
   int nbox = 0, nlevels = 0;
+  int max_u = 0;  // most U-list sources of a target leaf
   int64_t ns = 0, nt = 0;
   bool self = true;
   std::vector<int32_t> level_ptr;            // host copy
