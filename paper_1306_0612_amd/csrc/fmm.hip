@@ -936,8 +936,8 @@ __device__ __forceinline__ void p2l_pass_lds(int64_t xf0, int total,
   }
 }
 
-// M2L over the V list of every box with targets at level >= 2 (vector
-// ALU).  One 64-lane block per box; lane (g, l) accumulates coefficient l
+// M2L over the V list of every box with targets at level >= 2 (vector ALU;
+// FP32 orders other than 16).  One 64-lane block per box; lane (g, l) accumulates coefficient l
 // from every G-th list entry with the factorized translation
 // b_l += tau^-l sum_k H[l][k] (tau^-k a_k), H[l][k] = (-1)^k C(k+l-1, l).
 // The box's P2L sum over its X list (every box with an X list whose local
@@ -989,9 +989,8 @@ __global__ void __launch_bounds__(64)
     __syncthreads();
   }
   if (act) red[g][l] = acc;
-  // (xf_ptr null: no P2L here)
-  const int64_t xf0 = xf_ptr ? xf_ptr[b] : 0;
-  const int nx = xf_ptr ? (int)(xf_ptr[b + 1] - xf0) : 0;  // block-uniform
+  const int64_t xf0 = xf_ptr[b];
+  const int nx = (int)(xf_ptr[b + 1] - xf0);  // block-uniform
   if (nx > 0)
     p2l_pass_lds<T, P, 0>(xf0, nx, xf_idx, cxv[b], cyv[b], T(rad[b]), sx, sy,
                           p + (int64_t)r * ns, px, lane);
@@ -1994,7 +1993,7 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
                          gg);
     } else if constexpr (sizeof(T) == 8) {
       gamma_done = gg.nchunk > 0;
-      if (pl.x_box.n > 0 && !p2l_done)  // no upward pass
+      if (pl.x_box.n > 0 && !p2l_done)  // more boxes than the pass takes, or no pass
         hipLaunchKernelGGL((k_p2l64<P>), dim3((unsigned)(pl.x_box.n + 1) / 2, nrhs), dim3(64), 0,
                            s, x_boxes(pl), p, L, pl.nbox);
       launch_m2l64<P>(pl, H, M, L, true, nrhs, gg, s);
