@@ -96,7 +96,6 @@ void build_tables(Tables &t, int P, hipStream_t s) {
   t.pre64.upload(pre, s);
   t.post64.upload(post, s);
   t.h64.upload(h, s);
-  t.itp64.upload(itp, s);
   t.bc32.upload(to32(bc), s);
   t.pre32.upload(to32(pre), s);
   t.post32.upload(to32(post), s);
@@ -937,9 +936,10 @@ __device__ __forceinline__ void p2l_pass_lds(int64_t xf0, int total,
 }
 
 // M2L over the V list of every box with targets at level >= 2 (vector ALU;
-// FP32 orders other than 16).  One 64-lane block per box; lane (g, l) accumulates coefficient l
-// from every G-th list entry with the factorized translation
-// b_l += tau^-l sum_k H[l][k] (tau^-k a_k), H[l][k] = (-1)^k C(k+l-1, l).
+// FP32 orders other than 16).  One 64-lane block per box; lane (g, l)
+// accumulates coefficient l from every G-th list entry with the factorized
+// translation b_l += tau^-l sum_k H[l][k] (tau^-k a_k),
+// H[l][k] = (-1)^k C(k+l-1, l).
 // The box's P2L sum over its X list (every box with an X list whose local
 // expansion is used is one of these boxes) follows in the same block and
 // is added to the M2L result before the one store.
@@ -1933,16 +1933,14 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
                       const GammaFused *gf = nullptr) {
   bool gamma_done = false, p2l_done = false;
   StageTimer *tm = ws.timer;
-  const cx<T> *itp, *pre, *post;
+  const cx<T> *pre, *post;
   const T *H, *bc;
   if constexpr (sizeof(T) == 8) {
-    itp = (const cx<T> *)tb.itp64.p;
     H = (const T *)tb.h64.p;
     bc = (const T *)tb.bc64.p;
     pre = (const cx<T> *)tb.pre64.p;
     post = (const cx<T> *)tb.post64.p;
   } else {
-    itp = (const cx<T> *)tb.itp32.p;
     H = (const T *)tb.h32.p;
     bc = (const T *)tb.bc32.p;
     pre = (const cx<T> *)tb.pre32.p;
@@ -1989,8 +1987,8 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
       gamma_done = gg.nchunk > 0;
       hipLaunchKernelGGL(k_m2l_mfma16, dim3(groups, nrhs), dim3(256), 0, s,
                          pl.n_m2l, pl.m2l_wave.p, pl.v_ptr.p, pl.v_src.p,
-                         pl.v_code.p, H, itp, (const cx<T> *)M, L, pl.nbox, xs,
-                         gg);
+                         pl.v_code.p, H, (const cx<T> *)tb.itp32.p, (const cx<T> *)M, L,
+                         pl.nbox, xs, gg);
     } else if constexpr (sizeof(T) == 8) {
       gamma_done = gg.nchunk > 0;
       if (pl.x_box.n > 0 && !p2l_done)  // more boxes than the pass takes, or no pass
@@ -2000,7 +1998,8 @@ static bool far_field(const DevPlan &pl, const Tables &tb, Workspace &ws,
     } else {
       hipLaunchKernelGGL((k_m2l<T, P>), dim3(pl.n_m2l, nrhs), dim3(64), 0, s,
                          pl.m2l_box.p, pl.v_ptr.p, pl.v_src.p, pl.v_code.p, H,
-                         itp, (const cx<T> *)M, L, pl.nbox, pl.xf_ptr.p, pl.xf_idx.p,
+                         (const cx<T> *)tb.itp32.p, (const cx<T> *)M, L, pl.nbox, pl.xf_ptr.p,
+                         pl.xf_idx.p,
                          pl.cx.p, pl.cy.p, pl.rad.p, pl.sx.p, pl.sy.p, (const cx<T> *)p,
                          pl.ns);
     }

@@ -179,8 +179,8 @@ void build_m2l_groups(DevPlan &pl, const std::vector<int32_t> &grp, hipStream_t 
 struct Tables {
   int P = 0;
   // M2M / L2L: binomials (P x P, real) and the pre/post scale powers
-  // (4 x P, complex); M2L matrix H and inverse powers (itp)
-  DBuf<double> bc64, pre64, post64, h64, itp64;
+  // (4 x P, complex); M2L matrix H and, in FP32, inverse powers (itp)
+  DBuf<double> bc64, pre64, post64, h64;
   DBuf<float> bc32, pre32, post32, h32, itp32;
 };
 // Per-stage GPU timing with HIP events recorded on the launch stream.
