@@ -522,19 +522,17 @@ __device__ __forceinline__ void gamma_chunk(int c, int g, int r, int nch,
                                             double *__restrict__ csum,
                                             int32_t *__restrict__ cnt,
                                             double *__restrict__ gamma) {
-  __shared__ double red[8];
+  __shared__ double red[4];
   __shared__ bool last;
-  const int tid = threadIdx.x, nth = blockDim.x, slot = r * G + g;  // 64 .. 512 threads
+  const int tid = threadIdx.x, slot = r * G + g;  // (256 threads)
   const int a = gl_ptr[g] + c * kGammaChunk, b = min(gl_ptr[g + 1], a + kGammaChunk);
   double v = 0.0;
-  for (int e = a + tid; e < b; e += nth) v += gpart[(int64_t)r * nls + e];
+  for (int e = a + tid; e < b; e += 256) v += gpart[(int64_t)r * nls + e];
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if (tid < 8) red[tid] = 0.0;
-  __syncthreads();
   if ((tid & 63) == 0) red[tid >> 6] = v;
   __syncthreads();
   if (tid == 0) {
-    csum[(int64_t)slot * nch + c] = red[0] + red[1] + red[2] + red[3] + red[4] + red[5] + red[6] + red[7];
+    csum[(int64_t)slot * nch + c] = red[0] + red[1] + red[2] + red[3];
     __threadfence();
     last = atomicAdd(&cnt[slot], 1) == nch - 1;
   }
@@ -1185,7 +1183,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // wave waits for each row), a persistent form that reads one batch ahead 90
 // (158 registers, three waves a SIMD), groups of 32 entries 80; two and
 // eight waves a group 96 and 109 against 83 with four.
-constexpr int kM2LWaves = 4;
+constexpr int kM2LWaves = 4;  // (gamma_chunk takes 256 threads)
 template <int P>
 __global__ void __launch_bounds__(64 * kM2LWaves)
     k_m2l64(int ngrp, const int2 *__restrict__ ent, const int2 *__restrict__ gbox,
