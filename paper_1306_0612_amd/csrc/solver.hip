@@ -1321,8 +1321,6 @@ void launch_eval_logsrc(const Geometry &g, int64_t T, const double *txyz,
 // out[(v * R + r) * nseg + s] = sum_{i in segment s} a_v[r][i] b[r][i],
 // a_v[r][i] = a[v * lav + r * lac + i], b[r][i] = b[r * lbc + i].
 // Segments are unions of row chunks (seg of each chunk).
-constexpr int kChunkRows = 2048;
-
 __global__ void __launch_bounds__(256)
     k_seg_partial(const int64_t *__restrict__ c0, const int64_t *__restrict__ c1,
                   int nchunk, const double *__restrict__ a, int64_t lav,
