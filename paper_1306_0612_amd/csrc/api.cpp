@@ -489,10 +489,12 @@ struct lbs_ctx {
   DBuf<uint64_t> cg_keys;
   DBuf<int32_t> cg_ptr, cg_isl;
   DBuf<double> cg_zone;
-  // pinned: GMRES' iteration and active systems (k_gs_givens), and the
-  // number of active systems at a cycle's start behind it
+  // one pinned block: GMRES' iteration and active systems (k_gs_givens), the
+  // number of active systems at a cycle's start, and that of the targets
+  // without a neighbourhood (launch_locate_targets)
   uint64_t *word_host = nullptr;
   int32_t *count_host = nullptr;
+  int64_t *lone_host = nullptr;
   // pinned staging for target coordinates read back to the host
   double *stage_host = nullptr;
   size_t stage_n = 0;
@@ -1613,9 +1615,10 @@ lbs_ctx *setup_impl(int G, const int32_t *isl_per_geom, const lbs_island *isl_in
     if (host_timing()) LBS_HIP(hipStreamSynchronize(s));
   }
   ensure_ws(*ctx, 1, s);
-  LBS_HIP(hipHostMalloc((void **)&ctx->word_host, 128 + 2 * sizeof(int32_t),
+  LBS_HIP(hipHostMalloc((void **)&ctx->word_host, 3 * 128,
                         hipHostMallocMapped | hipHostMallocCoherent));
   ctx->count_host = reinterpret_cast<int32_t *>(ctx->word_host + 16);
+  ctx->lone_host = reinterpret_cast<int64_t *>(ctx->word_host + 32);
   LBS_HIP(hipStreamSynchronize(s));
   return ctx.release();
 }
@@ -1701,7 +1704,7 @@ EvalPlan &eval_plan(lbs_ctx &c, bool transposed, const std::vector<int64_t> &tof
     ep->lidx.alloc((size_t)n);
     ep->lone = launch_locate_targets(n, dtx.p, dty.p, ep->didx.p, G > 1 ? ep->dtgeo.p : nullptr,
                                      c.plan, ep->ltx.p, ep->lty.p, ep->lbox.p, ep->lroot.p,
-                                     ep->lidx.p, s);
+                                     ep->lidx.p, c.lone_host, s);
     if (transposed) {
       build_point_sources(c.plan, n, ep->ltx.p, ep->lty.p, ep->lbox.p, ep->lroot.p, ep->src, s);
       ep->located_src = true;

@@ -426,16 +426,15 @@ __global__ void __launch_bounds__(256)
 
 int64_t launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
                               const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
-                              int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s) {
+                              int32_t *obox, int32_t *oroot, int64_t *oidx, int64_t *lone,
+                              hipStream_t s) {
   if (n <= 0) return 0;
   if (n >= (int64_t)INT32_MAX) throw ApiError{LBS_ERR_UNSUPPORTED, "more than 2^31 targets"};
   DBuf<uint64_t> keys;
   DBuf<int32_t> vals;
-  DBuf<int64_t> dl;
   keys.alloc((size_t)n);
   vals.alloc((size_t)n);
-  dl.alloc(1);
-  launch_fill_int(2, 0, reinterpret_cast<int32_t *>(dl.p), s);
+  *lone = 0;
   const unsigned g = (unsigned)((n + 255) / 256);
   hipLaunchKernelGGL(k_locate, dim3(g), dim3(256), 0, s, n, tx, ty, idx, tgeo, pl.roots.p,
                      pl.cx.p, pl.cy.p, pl.rad.p, pl.lev.p, pl.child0.p, pl.nchild.p, pl.leaf.p,
@@ -444,12 +443,10 @@ int64_t launch_locate_targets(int64_t n, const double *tx, const double *ty, con
   while ((1ll << bits) <= (int64_t)pl.nbox) ++bits;
   sort_by_key(keys.p, vals.p, n, bits, s);
   hipLaunchKernelGGL(k_gather_located, dim3(g), dim3(256), 0, s, n, keys.p, vals.p, tx, ty, idx,
-                     tgeo, pl.roots.p, ox, oy, obox, oroot, oidx, dl.p);
+                     tgeo, pl.roots.p, ox, oy, obox, oroot, oidx, lone);
   LBS_HIP(hipGetLastError());
-  int64_t lone = 0;
-  LBS_HIP(hipMemcpyAsync(&lone, dl.p, sizeof(lone), hipMemcpyDeviceToHost, s));
   LBS_HIP(hipStreamSynchronize(s));  // keys, vals are released on return
-  return lone;
+  return *lone;
 }
 
 void launch_eval_points(int P, int64_t n, int64_t lone, const double *tx, const double *ty,

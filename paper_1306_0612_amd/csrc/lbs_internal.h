@@ -619,11 +619,13 @@ void sort_by_key(uint64_t *keys, int32_t *vals, int64_t n, int bits, SortBufs &s
 // Targets located in a plan's tree (evalpts.hip): the n targets (tx, ty;
 // API index idx; geometry tgeo[idx] or 0) sorted by the deepest box whose
 // square holds them (-1: the root or outside its square), with their roots
-// and API indices; returns the number of those with -1, which come first.
+// and API indices; returns the number of those with -1, which come first
+// (lone: a word of pinned memory for it).
 // The plan needs its tree links and roots on the device.
 int64_t launch_locate_targets(int64_t n, const double *tx, const double *ty, const int64_t *idx,
                               const int32_t *tgeo, const DevPlan &pl, double *ox, double *oy,
-                              int32_t *obox, int32_t *oroot, int64_t *oidx, hipStream_t s);
+                              int32_t *obox, int32_t *oroot, int64_t *oidx, int64_t *lone,
+                              hipStream_t s);
 // out[r ldy + tidx[i]] = scale Re sum_j p_j / (z_i - z_j) for located
 // targets (the first `lone` of them at -1), from the plan's FP64 expansions
 // M, L (order P) and strengths pstr of its sources (far_field already run for
