@@ -191,8 +191,7 @@ def stage_work(tree, n_nodes, P, fp64, pair_flop=FLOP_P2P_PAIR, nrhs=1):
         "upward": ("alu", FLOP_CMAC * P * n_nodes
                    + FLOP_CMAC * P * (P + 1) // 2 * (boxes - 1)),
         "l2l": ("alu", FLOP_CMAC * P * (P + 1) // 2 * (boxes - 1)),
-        "m2l": ("mfma" if not fp64 else "alu",
-                (4 * P * P + 14 * P) * tree["v_pairs"]),
+        "m2l": ("mfma", (4 * P * P + 14 * P) * tree["v_pairs"]),
         "p2l": ("alu", FLOP_CMAC * P * tree["p2l_evals"]),
         "leaf": ("alu", pair_flop * tree["p2p_interactions"]
                  + FLOP_CMAC * P * (n_nodes + tree["m2p_evals"])),

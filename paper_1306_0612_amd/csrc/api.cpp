@@ -651,7 +651,8 @@ int read_count(lbs_ctx &c, hipStream_t s) {
 
 // The number of systems active after iteration `it` of a cycle, as
 // k_gs_givens writes it to host memory.  A stream that has run dry or failed
-// without that write ends the wait.
+// without that write ends the wait.  (The thread is busy for the whole of a
+// solve, as it was in the synchronisations that this replaces.)
 int wait_count(lbs_ctx &c, uint32_t it, hipStream_t s) {
   for (uint32_t spin = 1;; ++spin) {
     const uint64_t w = __atomic_load_n(c.word_host, __ATOMIC_ACQUIRE);
@@ -694,10 +695,10 @@ std::vector<const void *> graph_signature(lbs_ctx &c) {
 // x = 0.  Classical Gram-Schmidt with `passes` passes (2: CGS2; 1 serves
 // the inner solves of mixed-precision refinement, which stop at a loose
 // tolerance and whose errors the FP64 outer residual corrects), Givens
-// rotations, one wait per iteration for the number of active systems.  With graph_id >= 0 (and graphs enabled, stage timing off)
-// the body of iteration k is captured once as a HIP graph under the key
-// (graph_id, R, k) and replayed afterwards; a graph_id always comes with
-// the same number of passes.
+// rotations, one wait per iteration for the number of active systems.  With
+// graph_id >= 0 (and graphs enabled, stage timing off) the body of iteration
+// k is captured once as a HIP graph under the key (graph_id, R, k) and
+// replayed afterwards; a graph_id always comes with the same number of passes.
 GmresOut gmres(lbs_ctx &c, const OpFn &op, int graph_id, int R, const double *b,
                double *x, bool x_zero, int max_iter, hipStream_t s, int passes) {
   GmresState &st = c.gm;

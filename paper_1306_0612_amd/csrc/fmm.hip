@@ -1176,13 +1176,15 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // in lane j + 16 (i % 4), register i / 4.
 //
 // Bound by the latency of the gathers and of the exchange; the matrix cores
-// are 0.4 busy (their share at 1.02M nodes, 536k entries: 30 of 75 us).  The
-// vector form this replaces broadcast y through LDS, 16 bytes read per two
-// multiply-adds and lane, four times what the LDS delivers beside them: 122
-// us.  Rows of H in scalar registers with one entry per lane took 105 us (a
-// wave waits for each row), a persistent form that reads one batch ahead 90
-// (158 registers, three waves a SIMD), groups of 32 entries 80; two and
-// eight waves a group 96 and 109 against 83 with four.
+// are 0.33 busy (counters over the benchmark's applications: 1.02M nodes,
+// 536k entries, about 93 us a launch; the vector form that this replaces took 168
+// with the P2L sums, which now take 43 in a launch of their own there).  That
+// form broadcast y through LDS, 16 bytes read per two multiply-adds and lane,
+// four times what the LDS delivers beside them.  Forms compared by repeated
+// applications on warm caches, where this one took 83 us: rows of H in scalar
+// registers with one entry per lane 105 (a wave waits for each row), a
+// persistent form that reads one batch ahead 90 (158 registers, three waves a
+// SIMD), two and eight waves a group 96 and 109; groups of 32 entries 80.
 constexpr int kM2LWaves = 4;  // (gamma_chunk takes 256 threads)
 template <int P>
 __global__ void __launch_bounds__(64 * kM2LWaves)
@@ -1442,12 +1444,17 @@ __device__ __forceinline__ void near_field64(int nt, int lg, int utot, int stage
 //
 // Bound by VALU issue at large node counts: 14 issue slots a pair (10 FP64
 // instructions, the reciprocal estimate four slots) over 218M pairs are 90
-// of its 161 us at 1.02M nodes (leaf 64).  One target per lane, which this
-// form replaces, read 32 bytes of LDS per pair and lane, as long as the
-// arithmetic takes, and read every expansion coefficient by a vector load
-// per lane: 184 us; 73 -> 28 us at 77k nodes and 45 -> 18 us at 20k, where
-// it left most of the chip idle.  Coefficients by scalar loads took 212 us
-// (a wave waits for each chunk), sources read one stage ahead 167 us.
+// us at 1.02M nodes (leaf 64), where the kernel takes about 175 in the benchmark's
+// applications (208 before) and 161 in repeated ones (184).  One target per
+// lane, which this form replaces, read 32 bytes of LDS per pair and lane, as
+// long as the arithmetic takes, and read every expansion coefficient by a
+// vector load per lane; at 77k nodes it took 73 us (now 28) and at 20k 45
+// (now 18), where it left most of the chip idle.  Coefficients by scalar
+// loads took 212 us (a wave waits for each chunk), sources read one stage
+// ahead 167.  Six waves per SIMD leave the real field of one column 80
+// registers, one too few: two are spilled, 16 MB of scratch writes a launch
+// beside the 9 MB of results.  The derivative's form keeps 40 bytes a lane in
+// scratch.
 template <int P, int MODE, int RB>
 __global__ void __launch_bounds__(256, MODE == kLeafField && RB == 1 ? 6 : 3)
     k_leaf64(const LeafHdr *__restrict__ hdr,

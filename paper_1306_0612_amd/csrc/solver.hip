@@ -1480,9 +1480,11 @@ void launch_gmres_start(int S, int m, const double *nrm2, const double *tol,
 
 // ------------------------------------------------ Gram-Schmidt of one step
 // One Arnoldi step orthogonalizes w against V_0 .. V_k (per system) in
-// three or four launches of these kernels, over row chunks that lie in one
-// segment (geometry) each; while a segment has few chunks a work-group adds
-// all their partial sums itself:
+// three (one pass) or four launches of these kernels, over row chunks that
+// lie in one segment (geometry) each.  While a segment has at most kGsFold
+// chunks a work-group adds all their partial sums itself; above that a
+// k_gs_reduce before every update does (four and six launches), and with two
+// passes over more than 56 columns the dots of the second take one more:
 //   k_gs_dots      partial sums of h1 = V^T w
 //   k_gs_update    w -= V h1, and (two passes) the partial sums of
 //                  h2 = V^T w with the entries of V still in registers
