@@ -67,6 +67,7 @@ struct DBuf {
     if (count == 0) return;
     hipError_t e = hipMalloc((void **)&p, count * sizeof(T));
     if (e != hipSuccess) {
+      (void)hipGetLastError();  // reported here, not by the caller's next call
       p = nullptr;
       n = 0;
       if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
