@@ -369,7 +369,7 @@ namespace lbs {
 void Workspace::ensure(const DevPlan &pl, int P64, int P32, int nrhs,
                        int64_t N, int M, int G, int Plog, hipStream_t s) {
   if (nrhs <= nrhs_cap) return;
-  nrhs_cap = nrhs;
+  nrhs_cap = 0;  // until every buffer is there (an allocation may throw)
   pstr64.alloc((size_t)pl.ns * nrhs * 2);
   mult64.alloc((size_t)pl.nbox * P64 * nrhs * 2);
   loc64.alloc((size_t)pl.nbox * P64 * nrhs * 2);
@@ -391,6 +391,7 @@ void Workspace::ensure(const DevPlan &pl, int P64, int P32, int nrhs,
   const size_t chunks = (size_t)((N + M) / 2048 + 2 * G + 4);
   red.alloc(std::max<size_t>((size_t)512 * std::max(nrhs, 128),
                              (size_t)128 * nrhs * chunks));
+  nrhs_cap = nrhs;
 }
 }  // namespace lbs
 
@@ -614,7 +615,7 @@ void ensure_gmres(lbs_ctx &c, int R) {
   if (st.R >= R && st.R > 0) return;
   const int m = c.opt.restart, G = c.geo.G, S = R * G;
   const int64_t n = c.geo.N + c.geo.M;
-  st.R = R;
+  st.R = 0;  // until every buffer is there (an allocation may throw)
   st.S = S;
   st.m = m;
   st.n = n;
@@ -640,6 +641,7 @@ void ensure_gmres(lbs_ctx &c, int R) {
   st.rvec.alloc((size_t)R * n);
   st.xvec.alloc((size_t)R * n);
   st.dvec.alloc((size_t)R * n);
+  st.R = R;
 }
 
 int read_count(lbs_ctx &c, hipStream_t s) {
